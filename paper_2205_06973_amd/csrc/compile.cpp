@@ -18,10 +18,12 @@
 // remaining tile bits (so that lanes touch neighbouring LDS slots and, in
 // the load and store layouts, neighbouring global addresses).
 //
-// Within a stage, runs of one-qubit gates on the same bit with no other
-// gate on that bit in between are multiplied into one 2x2 in FP64 (gates on
-// different bits commute, so the product can be applied where the run ends).
+// Runs of one-qubit gates on the same bit with no other gate on that bit in
+// between are multiplied into one 2x2 in FP64 (gates on different bits
+// commute, so the product can be applied where the run ends), and the 2x2
+// is split so that as little of it as possible runs (split_gate below).
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstring>
 
@@ -136,35 +138,174 @@ void emit_1q(int b, const cd u[4], std::vector<HostOp>* ops) {
   ops->push_back(op);
 }
 
-// Kind emit_1q gives u (-1: identity, no op).
-int kind_1q(const cd u[4]) {
-  if (is_exact(u[1], 0, 0) && is_exact(u[2], 0, 0)) {
-    if (is_exact(u[0], 1, 0) && is_exact(u[3], 1, 0)) return -1;
-    return is_exact(u[0], 1, 0) ? OP_D1 : OP_D;
-  }
-  if (is_exact(u[0], 0, 0) && is_exact(u[3], 0, 0) && is_exact(u[1], 1, 0) && is_exact(u[2], 1, 0))
-    return OP_X;
-  if (u[0].imag() == 0 && u[1].imag() == 0 && u[2].imag() == 0 && u[3].imag() == 0) return OP_R;
-  return OP_U;
+// ---- one-qubit gates as factors of the part's unitary ---------------------------
+//
+// A gate run pending on a bit is a 2x2 unitary M.  What the kernels spend on
+// it is vector instructions, and those depend on its entries: a term with
+// coefficient 1 costs nothing, -1 an add, a real or imaginary one one FMA a
+// component, a complex one two.  So M is written as S L K:
+//   S  a complex number.  It commutes with everything, is multiplied up over
+//      the part and goes into one op at the end.
+//   L  the factor that commutes with the two-qubit gate the bit meets next
+//      (diagonal for CZ, CP and a control; a rotation about X for a target).
+//      It stays pending and merges into the bit's next gate on the host.
+//   K  what has to run now, scaled so that its entries are 1 where possible:
+//      [[1, b], [-conj(b), 1]] for a generic M, 8 FMAs a pair of amplitudes
+//      instead of 16 multiplies and FMAs for M itself (a Hadamard: 4 adds; a
+//      rotation about one axis: 4 FMAs).
+// Instructions an amplitude of the specialized kernels, before and after: the
+// random circuit (30 qubits, k = 7) 2,192 and 1,062, layered 28 qubits, k = 6
+// 8,960 and 5,870, dressed pairs 9,992 and 4,476.  Layered 28 qubits complex64
+// specialized 83.0 -> 77.2 ms, 20 qubits 660 -> 541 us; the interpreter on 25
+// qubits complex128 11.64 -> 10.53 ms.
+// The amplitudes grow by 1/|S| on the way (at most a factor sqrt(2) an op);
+// past kMaxGrowth S goes into the op at hand, so that an unnormalised state
+// keeps all but 10 of its 127 (1023) binary orders of headroom.
+constexpr double kMaxGrowth = 1024.0;
+
+enum Role { kRoleZ, kRoleX, kRoleLast };  // kRoleLast: nothing may stay pending
+
+// The parts of a coefficient that are rounding noise of its computation (a
+// few units in the last place of its modulus) are set to zero, so that
+// products such as RZ H keep the real form of H.
+cd clean(const cd& z) {
+  constexpr double eps = 4.5e-16;
+  double re = z.real(), im = z.imag();
+  const double mag = std::max(std::fabs(re), std::fabs(im));
+  if (std::fabs(re) <= eps * mag) re = 0;
+  if (std::fabs(im) <= eps * mag) im = 0;
+  if (im == 0 && std::fabs(std::fabs(re) - 1.0) <= eps) re = std::copysign(1.0, re);
+  if (re == 0 && std::fabs(std::fabs(im) - 1.0) <= eps) im = std::copysign(1.0, im);
+  return cd(re, im);
 }
 
-// Estimated VALU instructions per wavefront for one op on A = 2^rb
-// amplitudes a lane: its arithmetic or register moves, plus what every op
-// costs the interpreter (moving the sub-state back into the loop's
-// registers, and the dispatch).
+// Vector instructions a pair of amplitudes (real and imaginary parts) for
+// y = K x when every term is written out.
+int pair_cost(const cd k[4]) {
+  int c = 0;
+  for (int r = 0; r < 2; ++r) {
+    int terms = 0;
+    bool unit = false;
+    for (int i = 0; i < 2; ++i) {
+      const cd& z = k[2 * r + i];
+      if (z == cd(0, 0)) continue;
+      terms += (z.real() != 0 && z.imag() != 0) ? 4 : 2;
+      unit |= std::fabs(z.real()) + std::fabs(z.imag()) == 1.0;
+    }
+    c += terms - (unit ? 2 : 0);
+  }
+  return c;
+}
+
+bool is_identity(const cd k[4]) {
+  return k[0] == cd(1, 0) && k[3] == cd(1, 0) && k[1] == cd(0, 0) && k[2] == cd(0, 0);
+}
+
+struct Split {
+  cd S = 1, K[4] = {1, 0, 0, 1}, L[4] = {1, 0, 0, 1};
+  int cost = 0;        // pair_cost(K)
+  double rank = 1e30;  // what the candidates are compared by
+};
+
+// M = S L K with L allowed by `role`; the cheapest of a few candidates.
+Split split_gate(const cd M[4], Role role) {
+  const cd a = M[0], b = M[1], c = M[2], d = M[3], zero(0, 0);
+  Split best;
+  auto offer = [&](cd S, cd l0, cd l1, cd l2, cd l3, cd k0, cd k1, cd k2, cd k3) {
+    Split s;
+    s.S = S;
+    const cd l[4] = {l0, l1, l2, l3}, k[4] = {k0, k1, k2, k3};
+    for (int i = 0; i < 4; ++i) {
+      s.L[i] = clean(l[i]);
+      s.K[i] = clean(k[i]);
+    }
+    s.cost = is_identity(s.K) ? 0 : pair_cost(s.K);
+    // a factor left pending may have to run later (up to 4); growth 1/|S|
+    s.rank = s.cost + (is_identity(s.L) ? 0.0 : 1.0) - 0.5 * std::log2(std::min(1.0, std::abs(S)));
+    if (s.rank < best.rank) best = s;
+  };
+  const bool diag = b == zero && c == zero, anti = a == zero && d == zero;
+  const double na = std::abs(a), nb = std::abs(b);
+  constexpr double kSmall = 0.125;
+  // nothing pending: M over one of its entries
+  if (na >= kSmall) offer(a, 1, 0, 0, 1, 1, b / a, c / a, d / a);
+  if (nb >= kSmall) offer(b, 1, 0, 0, 1, a / b, 1, c / b, d / b);
+  if (role == kRoleZ) {
+    if (diag) offer(a, 1, 0, 0, d / a, 1, 0, 0, 1);
+    else if (anti) offer(b, 1, 0, 0, c / b, 0, 1, 1, 0);
+    else {
+      if (na >= kSmall) offer(a, 1, 0, 0, d / a, 1, b / a, c / d, 1);
+      if (nb >= kSmall) offer(b, 1, 0, 0, c / b, a / b, 1, 1, d / c);
+    }
+  } else if (role == kRoleX) {
+    // M = e^{ig} (w - i (x X + y Y + z Z)); L = cos t - i sin t X with
+    // tan t = z / y leaves K without a Z component: [[w', -y'-ix'], [y'-ix', w']]
+    const cd ph = std::sqrt(a * d - b * c);
+    const cd u0 = a / ph, u1 = b / ph;
+    const double w = u0.real(), z = -u0.imag(), y = -u1.real(), x = -u1.imag();
+    const double r = std::hypot(y, z);
+    if (r <= 4.5e-16) {
+      offer(ph, cd(w, 0), cd(0, -x), cd(0, -x), cd(w, 0), 1, 0, 0, 1);
+    } else {
+      const double ct = y / r, sn = z / r;
+      const double w1 = w * ct + sn * x, x1 = x * ct - sn * w, y1 = r;
+      if (std::fabs(w1) >= kSmall)
+        offer(ph * w1, cd(ct, 0), cd(0, -sn), cd(0, -sn), cd(ct, 0), 1, cd(-y1, -x1) / w1, cd(y1, -x1) / w1, 1);
+    }
+  }
+  if (best.rank >= 1e30) {  // not a unitary: keep it as it is
+    for (int i = 0; i < 4; ++i) best.K[i] = M[i];
+    best.cost = pair_cost(best.K);
+  }
+  return best;
+}
+
+// Vector instructions an amplitude for one op on the kernels.
+double op_work(const HostOp& op) {
+  switch (op.kind) {
+    case OP_U: {
+      cd k[4];
+      for (int i = 0; i < 4; ++i) k[i] = cd(op.c[2 * i], op.c[2 * i + 1]);
+      return 0.5 * pair_cost(k);
+    }
+    case OP_R: {
+      cd k[4];
+      for (int i = 0; i < 4; ++i) k[i] = op.c[i];
+      return 0.5 * pair_cost(k);
+    }
+    case OP_D: return 4;
+    case OP_D1: return 2;
+    case OP_CP: return 1;
+    case OP_U2: return 16;
+    default: return 0;  // permutations and sign changes
+  }
+}
+
+// The interpreter's cost of an op on A = 2^rb amplitudes a lane: its
+// arithmetic (register moves for a permutation) and the dispatch.
 int op_cost(int kind, int A) {
   int c = 0;
   switch (kind) {
-    case -1: return 0;
-    case OP_U: c = 8 * A; break;
-    case OP_R: case OP_D: c = 4 * A; break;
-    case OP_D1: case OP_X: c = 2 * A; break;
-    case OP_CX: case OP_CP: case OP_SWAP: c = A; break;
-    case OP_CZ: c = A / 2; break;
+    case OP_CX: case OP_CP: case OP_SWAP: c = 2 * A; break;
+    case OP_CZ: c = A; break;
     case OP_U2: c = 16 * A; break;
     default: c = 8 * A;
   }
-  return c + A + 10;
+  return c + 10;
+}
+
+// The 2x2 of a one-qubit op.
+bool op_matrix(const HostOp& op, cd k[4]) {
+  k[0] = k[3] = 1;
+  k[1] = k[2] = 0;
+  switch (op.kind) {
+    case OP_U: for (int i = 0; i < 4; ++i) k[i] = cd(op.c[2 * i], op.c[2 * i + 1]); return true;
+    case OP_R: for (int i = 0; i < 4; ++i) k[i] = op.c[i]; return true;
+    case OP_D: k[0] = cd(op.c[0], op.c[1]); k[3] = cd(op.c[2], op.c[3]); return true;
+    case OP_D1: k[3] = cd(op.c[0], op.c[1]); return true;
+    case OP_X: k[0] = k[3] = 0; k[1] = k[2] = 1; return true;
+    default: return false;
+  }
 }
 
 // 4 x 4 matrices, basis index i = bit(b0) + 2 bit(b1), row-major.
@@ -229,6 +370,38 @@ void u2_apply_after(HostOp* op, int r0, const cd m[16]) {
   get_u2(*op, cur);
   matmul4(mm, cur, cur);
   set_u2(op, cur);
+}
+
+// Multiply the part's scalar S into the op where that adds the fewest
+// instructions (a dense 4 x 4 takes it for nothing, diag(1, d) costs the
+// other half of the amplitudes), or append it as a diagonal.
+void fold_scalar(const cd& S, std::vector<HostOp>* ops) {
+  if (clean(S) == cd(1, 0)) return;
+  int at = -1, cost = 8;  // a diagonal of its own: 8 instructions a pair
+  cd k[4], best[4] = {S, 0, 0, S};
+  for (int i = 0; i < (int)ops->size(); ++i) {
+    HostOp& op = (*ops)[i];
+    if (op.kind == OP_U2) {
+      cd m[16];
+      get_u2(op, m);
+      for (cd& z : m) z *= S;
+      set_u2(&op, m);
+      return;
+    }
+    if (!op_matrix(op, k)) continue;
+    const int before = op.kind == OP_X ? 0 : pair_cost(k);
+    for (cd& z : k) z = clean(z * S);
+    if (pair_cost(k) - before < cost) {
+      cost = pair_cost(k) - before;
+      at = i;
+      for (int j = 0; j < 4; ++j) best[j] = k[j];
+    }
+  }
+  std::vector<HostOp> made;
+  emit_1q(at < 0 ? 0 : (*ops)[at].b0, best, &made);
+  if (at < 0) ops->insert(ops->end(), made.begin(), made.end());
+  else if (!made.empty()) (*ops)[at] = made[0];
+  else (*ops)[at].kind = OP_D, (*ops)[at].c[0] = (*ops)[at].c[2] = 1, (*ops)[at].c[1] = (*ops)[at].c[3] = 0;
 }
 
 // Register-stage cut: seeded DFS orders tried per part.
@@ -333,6 +506,18 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
   int trips = 0;
   push_entry(load, nullptr);
   const Layout* prev = &load;
+  // One-qubit runs pending per tile bit.  A run stays pending over a change
+  // of stage when a later stage has gates on its bit.
+  cd pend[kMaxTile][4];
+  bool has[kMaxTile] = {false};
+  int last_stage[kMaxTile];
+  for (int t = 0; t < kMaxTile; ++t) last_stage[t] = -1;
+  for (size_t s = 0; s < st.size(); ++s)
+    for (int t = 0; t < m; ++t)
+      if (st[s].bits >> t & 1) last_stage[t] = (int)s;
+  cd scale = 1;  // the part's scalar S
+  const int A = 1 << rb;
+  const cd I2[4] = {1, 0, 0, 1};
   for (size_t s = 0; s < st.size(); ++s) {
     StageDesc* e = push_entry(lay[s], prev);
     trips += e->transition;
@@ -340,81 +525,116 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
     int reg_of[kMaxTile];
     for (int t = 0; t < kMaxTile; ++t) reg_of[t] = -1;
     for (int r = 0; r < rb; ++r) reg_of[lay[s].pos[lb + wb + r]] = r;
-    cd pend[kMaxTile][4];
-    bool has[kMaxTile] = {false};
-    // latest op on each register bit in this stage (-1: none): a dense
-    // 4 x 4 op that is still the latest on a bit absorbs later gates there
+    // latest op on each tile bit in this stage (-1: none): a dense 4 x 4 op
+    // that is still the latest on a bit absorbs later gates there
     int last[kMaxTile];
-    for (int r = 0; r < kMaxTile; ++r) last[r] = -1;
-    const int A = 1 << rb;
-    auto open_u2 = [&](int r) { return opt.fuse2 && last[r] >= 0 && out->ops[last[r]].kind == OP_U2; };
-    const cd I2[4] = {1, 0, 0, 1};
-    auto flush = [&](int r) {
-      if (!has[r]) return;
-      has[r] = false;
-      if (open_u2(r)) {
-        HostOp& o = out->ops[last[r]];
-        cd m[16];
-        kron2(r == o.b0 ? pend[r] : I2, r == o.b0 ? I2 : pend[r], m);
-        u2_apply_after(&o, o.b0, m);
+    for (int t = 0; t < kMaxTile; ++t) last[t] = -1;
+    auto open_u2 = [&](int t) { return opt.fuse2 && last[t] >= 0 && out->ops[last[t]].kind == OP_U2; };
+    // run what is pending on bit t, as far as `role` does not let it wait
+    auto flush = [&](int t, Role role) {
+      if (!has[t]) return;
+      if (open_u2(t)) {
+        has[t] = false;
+        HostOp& o = out->ops[last[t]];
+        cd m4[16];
+        kron2(reg_of[t] == o.b0 ? pend[t] : I2, reg_of[t] == o.b0 ? I2 : pend[t], m4);
+        u2_apply_after(&o, o.b0, m4);
         return;
       }
+      Split f = split_gate(pend[t], role);
+      scale *= f.S;
+      for (int j = 0; j < 4; ++j) pend[t][j] = f.L[j];
+      has[t] = !is_identity(f.L);
+      if (is_identity(f.K)) return;
+      if (std::abs(scale) < 1.0 / kMaxGrowth) {
+        for (cd& z : f.K) z *= scale;
+        scale = 1;
+      }
       const size_t before = out->ops.size();
-      emit_1q(r, pend[r], &out->ops);
-      if (out->ops.size() > before) last[r] = (int)before;
+      emit_1q(reg_of[t], f.K, &out->ops);
+      if (out->ops.size() > before) last[t] = (int)before;
     };
-    // cost of applying r's pending one-qubit gates on their own
-    auto pend_cost = [&](int r) { return (!has[r] || open_u2(r)) ? 0 : op_cost(kind_1q(pend[r]), A); };
-    for (int i : st[s].gates) {
-      const Gate& g = pg[i];
-      const int r0 = reg_of[bit_of[g.q0]];
+    // interpreter cost of what a two-qubit gate with this role makes run
+    auto pend_cost = [&](int t, Role role) {
+      if (!has[t] || open_u2(t)) return 0;
+      const int c = split_gate(pend[t], role).cost;
+      return c ? c * A / 2 + 10 : 0;
+    };
+    // the stage's next two-qubit gate on each of a gate's bits (-1: none)
+    std::vector<std::array<int, 2>> next(opt.fuse2 ? st[s].gates.size() : 0);
+    int upcoming[kMaxTile];
+    for (int t = 0; t < kMaxTile; ++t) upcoming[t] = -1;
+    for (int o = (int)next.size() - 1; o >= 0; --o) {
+      const Gate& g = pg[st[s].gates[o]];
+      if (g.arity() == 1) continue;
+      const int t0 = bit_of[g.q0], t1 = bit_of[g.q1];
+      next[o] = {upcoming[t0], upcoming[t1]};
+      upcoming[t0] = upcoming[t1] = o;
+    }
+    for (size_t o = 0; o < st[s].gates.size(); ++o) {
+      const Gate& g = pg[st[s].gates[o]];
+      const int t0 = bit_of[g.q0];
       if (g.arity() == 1) {
         cd u[4];
         gate_matrix(g, u);
-        if (has[r0]) {
-          matmul2(u, pend[r0], pend[r0]);
+        if (has[t0]) {
+          matmul2(u, pend[t0], pend[t0]);
         } else {
-          for (int j = 0; j < 4; ++j) pend[r0][j] = u[j];
-          has[r0] = true;
+          for (int j = 0; j < 4; ++j) pend[t0][j] = u[j];
+          has[t0] = true;
         }
         continue;
       }
-      const int r1 = reg_of[bit_of[g.q1]];
+      const int t1 = bit_of[g.q1];
+      const Role role1 = g.kind == HS_CX ? kRoleX : kRoleZ;
       if (opt.fuse2) {
-        cd m[16], pm[16];
-        if (hs_status rc = gate4(g, m)) return rc;
-        kron2(has[r0] ? pend[r0] : I2, has[r1] ? pend[r1] : I2, pm);
-        matmul4(m, pm, m);  // the pending one-qubit gates come first
+        cd m4[16], pm[16];
+        if (hs_status rc = gate4(g, m4)) return rc;
+        kron2(has[t0] ? pend[t0] : I2, has[t1] ? pend[t1] : I2, pm);
+        matmul4(m4, pm, m4);  // the pending one-qubit gates come first
+        const int r0 = reg_of[t0], r1 = reg_of[t1];
         const int gk = g.kind == HS_CX ? OP_CX : g.kind == HS_CZ ? OP_CZ : g.kind == HS_CP ? OP_CP : OP_SWAP;
-        if (open_u2(r0) && last[r0] == last[r1]) {  // same pair: absorb
-          u2_apply_after(&out->ops[last[r0]], r0, m);
-          has[r0] = has[r1] = false;
+        if (open_u2(t0) && last[t0] == last[t1]) {  // same pair: absorb
+          u2_apply_after(&out->ops[last[t0]], r0, m4);
+          has[t0] = has[t1] = false;
           continue;
         }
-        if (op_cost(OP_U2, A) < pend_cost(r0) + pend_cost(r1) + op_cost(gk, A)) {
+        // what a 4 x 4 op also saves: the bits' next gate, if it is on the
+        // same pair, or the run that a bit's last gate leaves pending
+        int saved = 0;
+        if (next[o][0] >= 0 && next[o][0] == next[o][1]) saved = 2 * (4 * A + 10) + op_cost(gk, A);
+        else
+          for (int j = 0; j < 2; ++j)
+            if (next[o][j] < 0 && last_stage[j ? t1 : t0] <= (int)s) saved += 6 * A + 10;
+        if (op_cost(OP_U2, A) < pend_cost(t0, kRoleZ) + pend_cost(t1, role1) + op_cost(gk, A) + saved) {
           HostOp op{};
           op.kind = OP_U2;
           op.b0 = std::min(r0, r1);
           op.b1 = std::max(r0, r1);
           cd mm[16];
           if (r0 < r1) {
-            for (int j = 0; j < 16; ++j) mm[j] = m[j];
+            for (int j = 0; j < 16; ++j) mm[j] = m4[j];
           } else {
-            swap_bits4(m, mm);
+            swap_bits4(m4, mm);
           }
           set_u2(&op, mm);
-          has[r0] = has[r1] = false;
-          last[r0] = last[r1] = (int)out->ops.size();
+          has[t0] = has[t1] = false;
+          last[t0] = last[t1] = (int)out->ops.size();
           out->ops.push_back(op);
           continue;
         }
       }
-      flush(r0);
-      flush(r1);
-      last[r0] = last[r1] = (int)out->ops.size();
+      if (g.kind == HS_SWAP) {  // what is pending moves with the qubits
+        std::swap(has[t0], has[t1]);
+        for (int j = 0; j < 4; ++j) std::swap(pend[t0][j], pend[t1][j]);
+      } else {
+        flush(t0, kRoleZ);
+        flush(t1, role1);
+      }
+      last[t0] = last[t1] = (int)out->ops.size();
       HostOp op{};
-      op.b0 = r0;
-      op.b1 = r1;
+      op.b0 = reg_of[t0];
+      op.b1 = reg_of[t1];
       switch (g.kind) {
         case HS_CX: op.kind = OP_CX; break;
         case HS_CZ: op.kind = OP_CZ; break;
@@ -428,7 +648,9 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
       }
       out->ops.push_back(op);
     }
-    for (int r = 0; r < rb; ++r) flush(r);
+    for (int t = 0; t < m; ++t)
+      if (reg_of[t] >= 0 && (open_u2(t) || last_stage[t] <= (int)s)) flush(t, kRoleLast);
+    if (s + 1 == st.size()) fold_scalar(scale, &out->ops);
     out->stages.back().op_end = (int)out->ops.size();
     prev = &lay[s];
   }
@@ -531,17 +753,15 @@ namespace hisv {
 // state = 1), fitted to per-part timings of 30-qubit states (random,
 // layered and dressed-pair circuits; 820 parts, mean |log error| 0.05): a
 // smooth maximum of the sweep (+0.04 / 0.02 per LDS re-layout, complex64 /
-// complex128) and the vector-ALU work -- 0.0065 / 0.005 sweep per flop per
-// amplitude (Sec. III.A's counting), plus 0.005 per register op for
-// complex128 (the dispatch; the register ops no longer copy the sub-state
-// back).  Used by AUTO only.
+// complex128) and the vector-ALU work -- 0.0114 / 0.00875 sweep per vector
+// instruction an amplitude (op_work), plus 0.005 per register op for
+// complex128 (the dispatch).  Used by AUTO only.
 double lds_part_cost(const CompiledPart& cp, hs_dtype dt) {
-  static const double flops[OP_NUM] = {14, 6, 6, 3, 0, 0, 0.5, 1.5, 0, 30};
   const bool f32 = dt == HS_C64;
   const double mem = 1.0 + (f32 ? 0.04 : 0.02) * cp.lds_round_trips;
   double f = 0;
-  for (const HostOp& op : cp.ops) f += flops[op.kind];
-  const double alu = (f32 ? 0.0065 : 0.005) * f + (f32 ? 0.0 : 0.005) * (double)cp.ops.size();
+  for (const HostOp& op : cp.ops) f += op_work(op);
+  const double alu = (f32 ? 0.0114 : 0.00875) * f + (f32 ? 0.0 : 0.005) * (double)cp.ops.size();
   return std::cbrt(mem * mem * mem + alu * alu * alu);
 }
 
@@ -550,16 +770,14 @@ double lds_part_cost(const CompiledPart& cp, hs_dtype dt) {
 // register permutations (X, CX, SWAP) are free (compile-time renames).
 // Heavier parts become vector-ALU bound.  Per-part timings of 30-qubit
 // states (random, layered and dressed-pair circuits, both precisions) fit
-// a smooth maximum of the sweep and 0.0045 sweep per flop per amplitude
-// (Sec. III.A's counting: a dense 2 x 2 is 14 flops per amplitude): flat at
-// ~1.1 sweeps below ~200 flops per amplitude, 1.6-1.7 at 350, 2.1-2.3 at
-// 500, 4.2-4.8 at 1,000.
+// a smooth maximum of the sweep and 0.0079 sweep per vector instruction an
+// amplitude (op_work: a dense 2 x 2 written out is 8): flat at ~1.1 sweeps
+// below ~110, 1.6-1.7 at 200, 2.1-2.3 at 285, 4.2-4.8 at 570.
 double spec_part_cost(const CompiledPart& cp, hs_dtype dt) {
-  static const double flops[OP_NUM] = {14, 6, 6, 3, 0, 0, 0.5, 1.5, 0, 30};
   const double mem = (dt == HS_C64 ? 1.05 : 1.0) + 0.03 * cp.lds_round_trips;
   double f = 0;
-  for (const HostOp& op : cp.ops) f += flops[op.kind];
-  const double alu = 0.0045 * f;
+  for (const HostOp& op : cp.ops) f += op_work(op);
+  const double alu = 0.0079 * f;
   return std::sqrt(std::sqrt(mem * mem * mem * mem + alu * alu * alu * alu));
 }
 

@@ -134,6 +134,46 @@ __device__ __forceinline__ void r_r(const RegV<T, RB>& a, RegV<T, RB>& b, const 
   }
 }
 
+// The scaled forms of a 2x2 (unit entries need no multiplication): 8 FMAs a
+// pair for K and P, 4 for KR and KI, 4 adds for H, 12 for W, against 16 for U
+// and 8 for R.
+template <typename T, int RB, int B, int KIND>
+__device__ __forceinline__ void r_k(const RegV<T, RB>& a, RegV<T, RB>& b, const T* __restrict__ c) {
+  const T c0 = c[0], c1 = c[1], c2 = c[2], c3 = c[3], c4 = c[4], c5 = c[5];
+#pragma unroll
+  for (int j = 0; j < (1 << RB); ++j) {
+    if (j & (1 << B)) continue;
+    const int k = j | (1 << B);
+    const T px = a[2 * j], py = a[2 * j + 1], qx = a[2 * k], qy = a[2 * k + 1];
+    T rx, ry, sx, sy;
+    if constexpr (KIND == OP_KR) {
+      rx = px + c0 * qx; ry = py + c0 * qy;
+      sx = qx + c1 * px; sy = qy + c1 * py;
+    } else if constexpr (KIND == OP_KI) {
+      rx = px - c0 * qy; ry = py + c0 * qx;
+      sx = qx - c1 * py; sy = qy + c1 * px;
+    } else if constexpr (KIND == OP_H) {
+      rx = px + qx; ry = py + qy;
+      sx = px - qx; sy = py - qy;
+    } else if constexpr (KIND == OP_P) {
+      rx = qx + c0 * px - c1 * py; ry = qy + c0 * py + c1 * px;
+      sx = px + c2 * qx - c3 * qy; sy = py + c2 * qy + c3 * qx;
+    } else {
+      rx = px + c0 * qx - c1 * qy; ry = py + c0 * qy + c1 * qx;
+      if constexpr (KIND == OP_K) {
+        sx = qx + c2 * px - c3 * py; sy = qy + c2 * py + c3 * px;
+      } else {  // OP_W
+        sx = c2 * px - c3 * py + c4 * qx - c5 * qy;
+        sy = c2 * py + c3 * px + c4 * qy + c5 * qx;
+      }
+    }
+    b[2 * j] = rx;
+    b[2 * j + 1] = ry;
+    b[2 * k] = sx;
+    b[2 * k + 1] = sy;
+  }
+}
+
 template <typename T, int RB, int B>
 __device__ __forceinline__ void r_d(const RegV<T, RB>& a, RegV<T, RB>& b, const T* __restrict__ c) {
   const T d0r = c[0], d0i = c[1], d1r = c[2], d1i = c[3];
@@ -239,6 +279,12 @@ __device__ __forceinline__ void apply_op(const RegV<T, RB>& a, RegV<T, RB>& b,
   switch (kind) {
     case OP_U: for_bit<RB>(b0, [&](auto B) __attribute__((always_inline)) { r_u<T, RB, decltype(B)::value>(a, b, c); }); break;
     case OP_R: for_bit<RB>(b0, [&](auto B) __attribute__((always_inline)) { r_r<T, RB, decltype(B)::value>(a, b, c); }); break;
+    case OP_K: for_bit<RB>(b0, [&](auto B) __attribute__((always_inline)) { r_k<T, RB, decltype(B)::value, OP_K>(a, b, c); }); break;
+    case OP_KR: for_bit<RB>(b0, [&](auto B) __attribute__((always_inline)) { r_k<T, RB, decltype(B)::value, OP_KR>(a, b, c); }); break;
+    case OP_KI: for_bit<RB>(b0, [&](auto B) __attribute__((always_inline)) { r_k<T, RB, decltype(B)::value, OP_KI>(a, b, c); }); break;
+    case OP_H: for_bit<RB>(b0, [&](auto B) __attribute__((always_inline)) { r_k<T, RB, decltype(B)::value, OP_H>(a, b, c); }); break;
+    case OP_P: for_bit<RB>(b0, [&](auto B) __attribute__((always_inline)) { r_k<T, RB, decltype(B)::value, OP_P>(a, b, c); }); break;
+    case OP_W: for_bit<RB>(b0, [&](auto B) __attribute__((always_inline)) { r_k<T, RB, decltype(B)::value, OP_W>(a, b, c); }); break;
     case OP_D: for_bit<RB>(b0, [&](auto B) __attribute__((always_inline)) { r_d<T, RB, decltype(B)::value>(a, b, c); }); break;
     case OP_D1: for_bit<RB>(b0, [&](auto B) __attribute__((always_inline)) { r_d1<T, RB, decltype(B)::value>(a, b, c); }); break;
     case OP_X: for_bit<RB>(b0, [&](auto B) __attribute__((always_inline)) { r_x<T, RB, decltype(B)::value>(a, b); }); break;
@@ -1051,6 +1097,39 @@ static IoOffsets interp_io(const StageDesc& e, const PartDesc& d) {
   return o;
 }
 
+// The interpreter's descriptor of an op: a dense or real 2x2 with unit entries
+// takes the form that leaves their multiplications out.
+template <typename T>
+static OpDesc<T> device_op(const HostOp& h) {
+  OpDesc<T> o{};
+  o.kind = h.kind;
+  o.b0 = h.b0;
+  o.b1 = h.b1;
+  for (int i = 0; i < 32; ++i) o.c[i] = (T)h.c[i];
+  if (h.kind != OP_U && h.kind != OP_R) return o;
+  cd u[4];
+  for (int i = 0; i < 4; ++i) u[i] = h.kind == OP_U ? cd(h.c[2 * i], h.c[2 * i + 1]) : cd(h.c[i], 0);
+  const cd one(1, 0);
+  auto set = [&](int kind, std::initializer_list<double> c) {
+    o.kind = kind;
+    std::fill(o.c, o.c + 32, T(0));
+    int i = 0;
+    for (double v : c) o.c[i++] = (T)v;
+  };
+  if (u[0] == one && u[3] == one) {
+    if (u[1].imag() == 0 && u[2].imag() == 0) set(OP_KR, {u[1].real(), u[2].real()});
+    else if (u[1].real() == 0 && u[2].real() == 0) set(OP_KI, {u[1].imag(), u[2].imag()});
+    else set(OP_K, {u[1].real(), u[1].imag(), u[2].real(), u[2].imag()});
+  } else if (u[0] == one && u[1] == one && u[2] == one && u[3] == -one) {
+    set(OP_H, {});
+  } else if (u[1] == one && u[2] == one) {
+    set(OP_P, {u[0].real(), u[0].imag(), u[3].real(), u[3].imag()});
+  } else if (u[0] == one && h.kind == OP_U) {
+    set(OP_W, {u[1].real(), u[1].imag(), u[2].real(), u[2].imag(), u[3].real(), u[3].imag()});
+  }
+  return o;
+}
+
 // Upload a plan's interpreter descriptors.  stream = NULL: hipMalloc and
 // blocking copies; otherwise the stream-ordered allocator and asynchronous
 // copies on `stream`, waited for before returning.
@@ -1087,12 +1166,7 @@ static hs_status upload_plan(Plan* p, int dtype, int dev, DevicePlan** out, hipS
     ip.n_stages = d.n_stages;
     for (int i = 0; i < kMaxTile; ++i) ip.tq[i] = d.tq[i];
     for (const HostOp& h : cp.ops) {
-      OpDesc<T> o{};
-      o.kind = h.kind;
-      o.b0 = h.b0;
-      o.b1 = h.b1;
-      for (int i = 0; i < 32; ++i) o.c[i] = (T)h.c[i];
-      ops.push_back(o);
+      ops.push_back(device_op<T>(h));
     }
     hparts.push_back(d);
     parts.push_back(ip);

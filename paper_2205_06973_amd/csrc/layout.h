@@ -58,7 +58,16 @@ enum OpKind : int32_t {
   OP_SWAP = 8,  // exchange bits b0 and b1
   OP_U2 = 9,    // dense 4x4 on b0 < b1, row/column index = bit b0 + 2 bit b1:
                 // c = 16 complex entries, row-major (32 reals)
-  OP_NUM = 10
+  OP_NUM = 10,
+  // Forms of OP_U and OP_R that the interpreter kernel runs with fewer
+  // instructions, chosen at upload (device_kind) from the coefficients.
+  // c holds b, c (complex; K_R: real, K_I: imaginary parts).
+  OP_K = 10,    // [[1, b], [c, 1]]
+  OP_KR = 11,   // the same with b, c real
+  OP_KI = 12,   // the same with b, c imaginary
+  OP_H = 13,    // [[1, 1], [1, -1]]
+  OP_P = 14,    // [[b, 1], [1, c]]
+  OP_W = 15     // [[1, b], [c, d]]: c = b, c, d
 };
 
 template <typename T>

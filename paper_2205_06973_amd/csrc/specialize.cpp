@@ -62,6 +62,32 @@ struct Emit {
   std::string T() const { return f32 ? "float" : "double"; }
 };
 
+// One component of c0 p + c1 q (c = re, im of both; p and q given by the
+// names of their parts): terms whose coefficient is zero are left out, +-1
+// needs no multiplication and comes first, so that each other term is one FMA.
+std::string row(const double* c, const char* px, const char* py, const char* qx, const char* qy, bool imag,
+                bool f32) {
+  struct Term {
+    double v;
+    const char* x;
+  };
+  const Term all[4] = {{c[0], imag ? py : px}, {imag ? c[1] : -c[1], imag ? px : py},
+                       {c[2], imag ? qy : qx}, {imag ? c[3] : -c[3], imag ? qx : qy}};
+  std::string out;
+  auto add = [&](const Term& t, bool unit) {
+    const bool neg = std::signbit(t.v);
+    if (out.empty()) out = neg ? "-" : "";
+    else out += neg ? " - " : " + ";
+    if (!unit) out += lit(std::fabs(t.v), f32) + "*";
+    out += t.x;
+  };
+  for (const Term& t : all)
+    if (std::fabs(t.v) == 1.0) add(t, true);
+  for (const Term& t : all)
+    if (t.v != 0.0 && std::fabs(t.v) != 1.0) add(t, false);
+  return out.empty() ? (f32 ? "0.0f" : "0.0") : out;
+}
+
 // a[j] register names: ar<j>, ai<j>
 void emit_op(Emit& E, const HostOp& op) {
   const int N = 1 << E.rb;
@@ -69,35 +95,22 @@ void emit_op(Emit& E, const HostOp& op) {
   const bool f = E.f32;
   auto L = [&](double v) { return lit(v, f); };
   switch (op.kind) {
-    case OP_U: {
-      const double* c = op.c;
-      for (int j = 0; j < N; ++j) {
-        if (j >> op.b0 & 1) continue;
-        const int k = j | (1 << op.b0);
-        o << "  { const " << E.T() << " px = ar" << j << ", py = ai" << j << ", qx = ar" << k
-          << ", qy = ai" << k << ";\n"
-          << "    ar" << j << " = " << L(c[0]) << "*px - " << L(c[1]) << "*py + " << L(c[2]) << "*qx - "
-          << L(c[3]) << "*qy;\n"
-          << "    ai" << j << " = " << L(c[0]) << "*py + " << L(c[1]) << "*px + " << L(c[2]) << "*qy + "
-          << L(c[3]) << "*qx;\n"
-          << "    ar" << k << " = " << L(c[4]) << "*px - " << L(c[5]) << "*py + " << L(c[6]) << "*qx - "
-          << L(c[7]) << "*qy;\n"
-          << "    ai" << k << " = " << L(c[4]) << "*py + " << L(c[5]) << "*px + " << L(c[6]) << "*qy + "
-          << L(c[7]) << "*qx; }\n";
-      }
-      break;
-    }
+    case OP_U:
     case OP_R: {
-      const double* c = op.c;
+      double c[8];  // complex entries u00 u01 u10 u11
+      for (int i = 0; i < 4; ++i) {
+        c[2 * i] = op.kind == OP_U ? op.c[2 * i] : op.c[i];
+        c[2 * i + 1] = op.kind == OP_U ? op.c[2 * i + 1] : 0.0;
+      }
       for (int j = 0; j < N; ++j) {
         if (j >> op.b0 & 1) continue;
         const int k = j | (1 << op.b0);
         o << "  { const " << E.T() << " px = ar" << j << ", py = ai" << j << ", qx = ar" << k
           << ", qy = ai" << k << ";\n"
-          << "    ar" << j << " = " << L(c[0]) << "*px + " << L(c[1]) << "*qx; ai" << j << " = "
-          << L(c[0]) << "*py + " << L(c[1]) << "*qy;\n"
-          << "    ar" << k << " = " << L(c[2]) << "*px + " << L(c[3]) << "*qx; ai" << k << " = "
-          << L(c[2]) << "*py + " << L(c[3]) << "*qy; }\n";
+          << "    ar" << j << " = " << row(c, "px", "py", "qx", "qy", false, f) << ";\n"
+          << "    ai" << j << " = " << row(c, "px", "py", "qx", "qy", true, f) << ";\n"
+          << "    ar" << k << " = " << row(c + 4, "px", "py", "qx", "qy", false, f) << ";\n"
+          << "    ai" << k << " = " << row(c + 4, "px", "py", "qx", "qy", true, f) << "; }\n";
       }
       break;
     }
@@ -124,9 +137,10 @@ void emit_op(Emit& E, const HostOp& op) {
           cr = op.c[0];
           ci = op.c[1];
         }
+        const double c[4] = {cr, ci, 0.0, 0.0};
         o << "  { const " << E.T() << " px = ar" << j << ", py = ai" << j << ";\n"
-          << "    ar" << j << " = px*" << L(cr) << " - py*" << L(ci) << "; ai" << j << " = px*" << L(ci)
-          << " + py*" << L(cr) << "; }\n";
+          << "    ar" << j << " = " << row(c, "px", "py", "", "", false, f) << "; ai" << j << " = "
+          << row(c, "px", "py", "", "", true, f) << "; }\n";
       }
       break;
     }
