@@ -111,18 +111,22 @@ typedef enum {
   HS_PART_CLOSURE = 4
 } hs_strategy;
 
-/* How hs_simulate applies a plan:
+/* How hs_simulate applies a plan.  The modes that work gate by gate (PART_LDS,
+ * PART_SPEC and AUTO's gate-by-gate side) may cut the whole plan's gates anew
+ * into pieces that fill a kernel tile, when that takes fewer sweeps than the
+ * plan has parts (hs_plan_num_sweeps reports how many); hs_simulate_part
+ * always applies the plan's own part.
  *   GATE_PER_PASS -- ignore the partition; one sweep of the state per gate
  *                    (the non-hierarchical case of Sec. III.B);
- *   PART_LDS      -- one sweep per part; each part runs gate by gate on
+ *   PART_LDS      -- one sweep per part or piece; each runs gate by gate on
  *                    register-resident sub-states, staged through LDS;
  *   PART_FUSED    -- one sweep per part; each part's gates are multiplied
  *                    into one dense 2^w x 2^w unitary applied on matrix cores;
- *   AUTO          -- per part, the cheaper by a cost model of PART_FUSED and
- *                    the gate-by-gate kernel: PART_SPEC's when
- *                    hs_plan_specialize has built them for the state's dtype
- *                    and device, else PART_LDS's;
- *   PART_SPEC     -- one sweep per part, as PART_LDS, with each part's kernel
+ *   AUTO          -- the cheapest by a cost model: the pieces gate by gate, or
+ *                    per part PART_FUSED or the gate-by-gate kernel;
+ *                    PART_SPEC's kernels where they have been built for the
+ *                    state's dtype and device, else PART_LDS's;
+ *   PART_SPEC     -- sweeps as in PART_LDS, with each one's kernel
  *                    specialized at plan time: the part's layouts, register
  *                    operations and coefficients become compile-time
  *                    constants of a kernel built with hipRTC for gfx950
@@ -311,15 +315,27 @@ hs_status hs_plan_part_descriptors(hs_plan p, int part, hs_dtype dtype, hs_exec 
 hs_status hs_plan_part_source(hs_plan p, int part, hs_dtype dtype, char* buf, size_t cap,
                               size_t* len);
 
-/* Build (hipRTC, in parallel) and load the PART_SPEC kernels of every part
- * for `dtype` on the current device.  Kernels are cached per device by their
- * source, so plans sharing parts share kernels.  HS_E_HIP with the compiler
- * log on failure. */
+/* Sweeps of the state that hs_simulate makes for the plan with `dtype` and
+ * `exec` (AUTO: with the kernels built so far on the current device): the
+ * pieces it cuts the plan's gates into, the parts where it keeps them, one per
+ * gate for GATE_PER_PASS. */
+hs_status hs_plan_num_sweeps(hs_plan p, hs_dtype dtype, hs_exec exec, int* out);
+
+/* hs_plan_part_source for sweep number `sweep` of hs_simulate with PART_SPEC
+ * (0 <= sweep < hs_plan_num_sweeps). */
+hs_status hs_plan_sweep_source(hs_plan p, int sweep, hs_dtype dtype, char* buf, size_t cap,
+                               size_t* len);
+
+/* Build (hipRTC) and load the PART_SPEC kernels that hs_simulate runs for the
+ * plan and `dtype` on the current device: those of its sweeps.  (The kernels
+ * of single parts, where they differ, are built by the first hs_simulate_part
+ * with PART_SPEC.)  Kernels are cached per device by their source, so plans
+ * sharing sweeps share kernels.  HS_E_HIP with the compiler log on failure. */
 hs_status hs_plan_specialize(hs_plan p, hs_dtype dtype);
 
 /* hs_plan_specialize on a host thread of the library: returns at once (after
  * the part compile, so that a compile error is reported here).  While the
- * kernels build, HS_EXEC_AUTO runs the plan's gate-by-gate parts on the
+ * kernels build, HS_EXEC_AUTO runs gate-by-gate sweeps on the
  * interpreter kernel; once they are built it uses them.  A circuit run once
  * therefore never waits for hipRTC, and one run many times moves to the
  * specialized kernels after the build.  HS_EXEC_PART_SPEC waits for the build.
@@ -345,7 +361,8 @@ hs_status hs_plan_specialized(hs_plan p, hs_dtype dtype, int* ready);
 hs_status hs_plan_part_unitary(hs_plan p, int part, int* w, double* out);
 
 /* Which kernel HS_EXEC_AUTO runs for each part of `p` at `dtype` on the
- * current device: out[part] = 1 for the fused dense-unitary kernel, 0 for
+ * current device, in hs_simulate_part and where hs_simulate keeps the plan's
+ * parts: out[part] = 1 for the fused dense-unitary kernel, 0 for
  * the gate-by-gate kernel (the specialized one if the plan has been
  * specialized for `dtype` on this device, else the interpreter).  AUTO picks
  * per part the lower of the two cost estimates, in HBM sweeps of the state:
@@ -359,9 +376,10 @@ hs_status hs_plan_destroy(hs_plan p);
 
 /* ---- simulation (Alg. 1) --------------------------------------------------- */
 
-/* Apply the plan's circuit to the state, part after part in id order, each
- * part as one sweep (Alg. 1), or one sweep per gate for GATE_PER_PASS.
- * Asynchronous on the state's stream.  HS_E_ARG if the plan's n differs
+/* Apply the plan's circuit to the state: the parts in id order or the pieces
+ * hs_simulate cuts the plan's gates into (see hs_exec), each as one sweep
+ * (Alg. 1), or one sweep per gate for GATE_PER_PASS.  The first call groups
+ * and compiles them.  Asynchronous on the state's stream.  HS_E_ARG if the plan's n differs
  * from the state's; HS_E_UNSUPPORTED if a part exceeds hs_max_part_qubits. */
 hs_status hs_simulate(hs_state s, hs_plan p, hs_exec exec);
 

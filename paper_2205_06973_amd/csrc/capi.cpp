@@ -26,8 +26,9 @@ namespace hisv {
 Plan::~Plan() {
   for (std::thread& t : spec_threads)
     if (t.joinable()) t.join();
-  for (int d = 0; d < 2; ++d)
-    for (auto& kv : dev[d]) device_plan_free(kv.second);
+  for (auto& of : dev)
+    for (auto& by_device : of)
+      for (auto& kv : by_device) device_plan_free(kv.second);
 }
 
 // Tunable knobs (hs_tune), read when a plan is compiled.  Register bits per
@@ -142,7 +143,9 @@ static hs_status compile_all(Plan* p, const CompileOptions& opt, std::vector<Com
 hs_status plan_compile(Plan* p, hs_dtype dtype) {
   std::lock_guard<std::mutex> lk(p->mu);
   if (p->compiled[dtype]) return HS_OK;
-  if (hs_status rc = compile_all(p, default_options(dtype, false), &p->comp[dtype])) return rc;
+  CompileOptions opt = default_options(dtype, false);
+  opt.plain = p->plain(dtype, false);
+  if (hs_status rc = compile_all(p, opt, &p->comp[dtype])) return rc;
   p->compiled[dtype] = true;
   return HS_OK;
 }
@@ -573,27 +576,45 @@ hs_status hs_plan_part_descriptors(hs_plan p, int part, hs_dtype dtype, hs_exec 
   });
 }
 
-// The plan's specialized kernels for `dtype` on `device`, built if need be.
-// The build runs under the plan's build lock only, so the interpreter and
-// AUTO keep launching parts (they take p->mu briefly) while hipRTC works.
-static hs_status ensure_spec(Plan* p, hs_dtype dtype, int device,
+// The specialized kernels of a plan's parts or sweeps for `dtype` on `device`,
+// built if need be.  The build runs under the plan's build lock only, so the
+// interpreter and AUTO keep launching parts (they take p->mu briefly) while
+// hipRTC works.
+static hs_status ensure_spec(Plan* p, bool sweep, hs_dtype dtype, int device,
                              std::vector<std::shared_ptr<SpecKernel>>** out) {
-  if (hs_status rc = plan_compile_spec(p, dtype)) return rc;
+  // neither list changes any more once compiled
+  const std::vector<CompiledPart>* comp = &p->scomp[dtype];
+  if (sweep) {
+    const SweepSet* set = nullptr;
+    if (hs_status rc = plan_sweeps(p, dtype, true, &set)) return rc;
+    comp = &set->comp;
+  } else if (hs_status rc = plan_compile_spec(p, dtype)) {
+    return rc;
+  }
   std::lock_guard<std::mutex> build(p->spec_build_mu);
   {
     std::lock_guard<std::mutex> lk(p->mu);
-    auto it = p->spec[dtype].find(device);
-    if (it != p->spec[dtype].end()) {
+    auto it = p->spec[sweep][dtype].find(device);
+    if (it != p->spec[sweep][dtype].end()) {
       *out = &it->second;
       return HS_OK;
     }
   }
-  // scomp[dtype] no longer changes once compiled
   std::vector<std::shared_ptr<SpecKernel>> ks;
-  if (hs_status rc = specialize_plan(p->scomp[dtype], dtype, device, &ks)) return rc;
+  if (hs_status rc = specialize_plan(*comp, dtype, device, &ks)) return rc;
   std::lock_guard<std::mutex> lk(p->mu);
-  *out = &p->spec[dtype].emplace(device, std::move(ks)).first->second;
+  *out = &p->spec[sweep][dtype].emplace(device, std::move(ks)).first->second;
   return HS_OK;
+}
+
+// The kernels hs_simulate runs for a plan on `device`: its sweeps' where it has
+// sweeps, its parts' otherwise.
+static hs_status ensure_spec_plan(Plan* p, hs_dtype dtype, int device, bool* sweep,
+                                  std::vector<std::shared_ptr<SpecKernel>>** out) {
+  const SweepSet* set = nullptr;
+  if (hs_status rc = plan_sweeps(p, dtype, true, &set)) return rc;
+  *sweep = !set->comp.empty();
+  return ensure_spec(p, *sweep, dtype, device, out);
 }
 
 hs_status hs_plan_part_source(hs_plan p, int part, hs_dtype dtype, char* buf, size_t cap, size_t* len) {
@@ -618,7 +639,8 @@ hs_status hs_plan_specialize(hs_plan p, hs_dtype dtype) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return fail(HS_E_HIP, "no HIP device");
     std::vector<std::shared_ptr<SpecKernel>>* ks = nullptr;
-    return ensure_spec(p, dtype, dev, &ks);
+    bool sweep = false;
+    return ensure_spec_plan(p, dtype, dev, &sweep, &ks);
   });
 }
 
@@ -630,16 +652,20 @@ hs_status hs_plan_specialize_async(hs_plan p, hs_dtype dtype) {
     if (hipGetDevice(&dev) != hipSuccess) return fail(HS_E_HIP, "no HIP device");
     // the descriptors first, on the caller's thread (host work, milliseconds),
     // so that a compile error is reported here
-    if (hs_status rc = plan_compile_spec(p, dtype)) return rc;
+    const SweepSet* set = nullptr;
+    if (hs_status rc = plan_sweeps(p, dtype, true, &set)) return rc;
+    const bool sweep = !set->comp.empty();
+    if (!sweep)
+      if (hs_status rc = plan_compile_spec(p, dtype)) return rc;
     std::lock_guard<std::mutex> lk(p->mu);
-    if (p->spec[dtype].count(dev)) return HS_OK;
+    if (p->spec[sweep][dtype].count(dev)) return HS_OK;
     p->spec_async_rc[dtype] = HS_OK;
     p->spec_async_msg[dtype].clear();
     Plan* plan = p;
-    p->spec_threads.emplace_back([plan, dtype, dev]() {
+    p->spec_threads.emplace_back([plan, sweep, dtype, dev]() {
       std::vector<std::shared_ptr<SpecKernel>>* ks = nullptr;
       hs_status rc = guarded([&] {
-        return hipSetDevice(dev) == hipSuccess ? ensure_spec(plan, dtype, dev, &ks)
+        return hipSetDevice(dev) == hipSuccess ? ensure_spec(plan, sweep, dtype, dev, &ks)
                                                : fail(HS_E_HIP, "hipSetDevice failed");
       });
       if (rc != HS_OK) {
@@ -680,18 +706,19 @@ hs_status hs_plan_specialized(hs_plan p, hs_dtype dtype, int* ready) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return fail(HS_E_HIP, "no HIP device");
     std::lock_guard<std::mutex> lk(p->mu);
-    *ready = p->spec[dtype].count(dev) ? 1 : 0;
+    const SweepSet& set = p->sweeps[1][dtype];  // grouped by now if anything was built
+    *ready = p->spec[set.ready && !set.comp.empty()][dtype].count(dev) ? 1 : 0;
     return HS_OK;
   });
 }
 
-static hs_status run_spec_parts(hs_state s, Plan* p, int first, int last) {
-  std::vector<std::shared_ptr<SpecKernel>>* ks = nullptr;
+// Kernels [first, last) of a plan's parts or sweeps.
+static hs_status launch_spec(hs_state s, Plan* p, bool sweep, const std::vector<std::shared_ptr<SpecKernel>>& ks,
+                             int first, int last) {
   if (hipSetDevice(s->device) != hipSuccess) return fail(HS_E_HIP, "hipSetDevice failed");
-  if (hs_status rc = ensure_spec(p, s->dtype, s->device, &ks)) return rc;
+  const std::vector<CompiledPart>& comp = sweep ? p->sweeps[1][s->dtype].comp : p->scomp[s->dtype];
   for (int i = first; i < last; ++i)
-    if (hs_status rc = launch_specialized(*(*ks)[i], p->scomp[s->dtype][i], s->ptr, s->stream))
-      return rc;
+    if (hs_status rc = launch_specialized(*ks[i], comp[i], s->ptr, s->stream)) return rc;
   return HS_OK;
 }
 
@@ -711,50 +738,144 @@ static hs_status check_exec(hs_exec exec) {
   return fail(HS_E_ARG, "unknown exec mode %d", (int)exec);
 }
 
-// Parts [first, last) on the interpreter LDS kernel, the fused kernel, or
-// (AUTO) whichever the cost model prefers per part.  AUTO's gate-by-gate side
-// is the specialized kernels when hs_plan_specialize has built them for this
-// dtype and device (no hipRTC work starts here), else the interpreter.
-// AUTO's choice for part i: the fused kernel when the part has a fused form
-// and its cost (in HBM sweeps) is below the gate-by-gate kernel's -- the
-// specialized kernel's when the plan is specialized, else the interpreter's.
-static bool auto_picks_fused(Plan* p, hs_dtype dt, int i, bool specialized) {
-  const double gate_cost = specialized ? spec_part_cost(p->scomp[dt][i], dt) : lds_part_cost(p->comp[dt][i], dt);
-  return p->fused[i].w && fused_part_cost(p->fused[i], dt) < gate_cost;
+// The specialized kernels of a plan's parts or sweeps, if they are built on
+// `device` (no hipRTC work starts here), else null.
+static const std::vector<std::shared_ptr<SpecKernel>>* built_spec(Plan* p, bool sweep, hs_dtype dt, int device) {
+  std::lock_guard<std::mutex> lk(p->mu);
+  auto it = p->spec[sweep][dt].find(device);
+  return it == p->spec[sweep][dt].end() ? nullptr : &it->second;
 }
 
+// AUTO's cost of part i, in HBM sweeps, on the fused kernel and gate by gate
+// (the specialized kernel where the parts' are built, else the interpreter).
+static double fused_cost(const Plan* p, hs_dtype dt, int i) { return fused_part_cost(p->n, p->masks[i], dt); }
+static double gate_cost(const Plan* p, hs_dtype dt, int i, bool specialized) {
+  return specialized ? spec_part_cost(p->scomp[dt][i], dt) : lds_part_cost(p->comp[dt][i], dt);
+}
+static bool auto_picks_fused(const Plan* p, hs_dtype dt, int i, bool specialized) {
+  return fused_cost(p, dt, i) < gate_cost(p, dt, i, specialized);
+}
+
+// Parts [first, last): PART_LDS on the interpreter, PART_FUSED on the fused
+// kernel, AUTO on whichever the cost model prefers per part.
 static hs_status run_parts(hs_state s, Plan* p, int first, int last, hs_exec exec) {
   if (hs_status rc = plan_compile(p, s->dtype)) return rc;
-  if (exec != HS_EXEC_PART_LDS)
-    if (hs_status rc = plan_compile_fused(p)) return rc;
-  std::vector<std::shared_ptr<SpecKernel>>* ks = nullptr;
-  if (exec == HS_EXEC_AUTO) {
-    std::lock_guard<std::mutex> lk(p->mu);
-    auto it = p->spec[s->dtype].find(s->device);
-    if (it != p->spec[s->dtype].end()) ks = &it->second;
-  }
+  const std::vector<std::shared_ptr<SpecKernel>>* ks =
+      exec == HS_EXEC_AUTO ? built_spec(p, false, s->dtype, s->device) : nullptr;
   for (int i = first; i < last; ++i) {
-    bool fused = false;
-    if (exec == HS_EXEC_PART_FUSED) {
-      if (!p->fused[i].w)
-        return fail(HS_E_UNSUPPORTED, "part %d uses more than %d qubits: no fused form", i,
-                    kMaxFusedQubits);
-      fused = true;
-    } else if (exec == HS_EXEC_AUTO) {
-      fused = auto_picks_fused(p, s->dtype, i, ks != nullptr);
-    }
+    const bool fused = exec == HS_EXEC_PART_FUSED ||
+                       (exec == HS_EXEC_AUTO && auto_picks_fused(p, s->dtype, i, ks != nullptr));
     hs_status rc;
     if (fused) {
+      if ((rc = plan_compile_fused(p))) return rc;
+      if (!p->fused[i].w)
+        return fail(HS_E_UNSUPPORTED, "part %d uses more than %d qubits: no fused form", i, kMaxFusedQubits);
       rc = dev_run_fused(s, p, i);
     } else if (ks) {
-      if (hipSetDevice(s->device) != hipSuccess) return fail(HS_E_HIP, "hipSetDevice failed");
-      rc = launch_specialized(*(*ks)[i], p->scomp[s->dtype][i], s->ptr, s->stream);
+      rc = launch_spec(s, p, false, *ks, i, i + 1);
     } else {
       rc = dev_run_part(s, p, i);
     }
     if (rc) return rc;
   }
   return HS_OK;
+}
+
+static hs_status run_spec_part(hs_state s, Plan* p, int part) {
+  std::vector<std::shared_ptr<SpecKernel>>* ks = nullptr;
+  if (hipSetDevice(s->device) != hipSuccess) return fail(HS_E_HIP, "hipSetDevice failed");
+  if (hs_status rc = ensure_spec(p, false, s->dtype, s->device, &ks)) return rc;
+  return launch_spec(s, p, false, *ks, part, part + 1);
+}
+
+// What hs_simulate runs for a whole plan in modes PART_LDS, PART_SPEC and
+// AUTO: the plan's sweeps (`set`) or its parts, and on `ks` if they are
+// specialized kernels.  Only PART_SPEC builds kernels here.
+struct WholePlan {
+  const SweepSet* set = nullptr;
+  const std::vector<std::shared_ptr<SpecKernel>>* ks = nullptr;
+  bool sweep = false;
+};
+static hs_status choose_whole(Plan* p, hs_dtype dt, int device, hs_exec exec, bool build, WholePlan* w) {
+  const bool spec = exec == HS_EXEC_PART_SPEC;
+  w->ks = exec == HS_EXEC_AUTO ? built_spec(p, true, dt, device) : nullptr;
+  double parts = 0;  // AUTO: the parts, each on its cheaper kernel
+  if (exec == HS_EXEC_AUTO) {
+    if (hs_status rc = plan_compile(p, dt)) return rc;
+    const bool parts_built = built_spec(p, false, dt, device) != nullptr;
+    double alu = 0;
+    for (int i = 0; i < (int)p->parts.size(); ++i) {
+      parts += std::min(fused_cost(p, dt, i), gate_cost(p, dt, i, parts_built));
+      alu += lds_part_alu(p->comp[dt][i], dt);
+    }
+    // the interpreter's arithmetic hardly changes with the cut (the sweeps
+    // save up to a tenth): where it alone costs more, nothing is regrouped
+    if (!w->ks && 0.9 * alu > parts) return HS_OK;
+  }
+  if (hs_status rc = plan_sweeps(p, dt, spec || w->ks, &w->set)) return rc;
+  w->sweep = !w->set->comp.empty();
+  if (spec && build) {
+    std::vector<std::shared_ptr<SpecKernel>>* ks = nullptr;
+    if (hs_status rc = ensure_spec(p, w->sweep, dt, device, &ks)) return rc;
+    w->ks = ks;
+  }
+  if (w->sweep && exec == HS_EXEC_AUTO) {
+    double sweeps = 0;
+    for (const CompiledPart& cp : w->set->comp) sweeps += w->ks ? spec_part_cost(cp, dt) : lds_part_cost(cp, dt);
+    w->sweep = sweeps <= parts;
+  }
+  return HS_OK;
+}
+
+static hs_status run_plan(hs_state s, Plan* p, hs_exec exec) {
+  const int P = (int)p->parts.size();
+  if (exec == HS_EXEC_PART_FUSED) return run_parts(s, p, 0, P, exec);
+  if (hipSetDevice(s->device) != hipSuccess) return fail(HS_E_HIP, "hipSetDevice failed");
+  WholePlan w;
+  if (hs_status rc = choose_whole(p, s->dtype, s->device, exec, true, &w)) return rc;
+  if (exec == HS_EXEC_PART_SPEC || (w.sweep && w.ks)) return launch_spec(s, p, w.sweep, *w.ks, 0, (int)w.ks->size());
+  if (!w.sweep) return run_parts(s, p, 0, P, exec);
+  for (int i = 0; i < (int)w.set->comp.size(); ++i)
+    if (hs_status rc = dev_run_part(s, p, i, true)) return rc;
+  return HS_OK;
+}
+
+hs_status hs_plan_num_sweeps(hs_plan p, hs_dtype dtype, hs_exec exec, int* out) {
+  return guarded([&]() -> hs_status {
+    CHECK_ARG(p && out, "null argument");
+    CHECK_ARG(dtype == HS_C64 || dtype == HS_C128, "bad dtype %d", (int)dtype);
+    if (hs_status rc = check_exec(exec)) return rc;
+    if (exec == HS_EXEC_GATE_PER_PASS || exec == HS_EXEC_PART_FUSED) {
+      *out = (int)(exec == HS_EXEC_PART_FUSED ? p->parts.size() : p->gates.size());
+      return HS_OK;
+    }
+    int device = 0;
+    if (hipGetDevice(&device) != hipSuccess) device = -1;
+    WholePlan w;
+    if (hs_status rc = choose_whole(p, dtype, device, exec, false, &w)) return rc;
+    *out = (int)(w.sweep ? w.set->comp.size() : p->parts.size());
+    return HS_OK;
+  });
+}
+
+hs_status hs_plan_sweep_source(hs_plan p, int sweep, hs_dtype dtype, char* buf, size_t cap, size_t* len) {
+  return guarded([&]() -> hs_status {
+    CHECK_ARG(p, "null plan");
+    CHECK_ARG(dtype == HS_C64 || dtype == HS_C128, "bad dtype");
+    const SweepSet* set = nullptr;
+    if (hs_status rc = plan_sweeps(p, dtype, true, &set)) return rc;
+    if (set->comp.empty()) {
+      if (hs_status rc = plan_compile_spec(p, dtype)) return rc;
+    }
+    const std::vector<CompiledPart>& comp = set->comp.empty() ? p->scomp[dtype] : set->comp;
+    CHECK_ARG(sweep >= 0 && sweep < (int)comp.size(), "sweep %d out of range", sweep);
+    const std::string src = specialize_part_source(comp[sweep], dtype, "part_pass_spec");
+    if (len) *len = src.size();
+    if (!buf) return HS_OK;
+    CHECK_ARG(cap > src.size(), "buffer of %zu bytes is too small", cap);
+    std::memcpy(buf, src.c_str(), src.size() + 1);
+    return HS_OK;
+  });
 }
 
 hs_status hs_simulate_part(hs_state s, hs_plan p, int part, hs_exec exec) {
@@ -768,7 +889,7 @@ hs_status hs_simulate_part(hs_state s, hs_plan p, int part, hs_exec exec) {
         if (hs_status rc = dev_gate_pass(s, p->gates[gi])) return rc;
       return HS_OK;
     }
-    if (exec == HS_EXEC_PART_SPEC) return run_spec_parts(s, p, part, part + 1);
+    if (exec == HS_EXEC_PART_SPEC) return run_spec_part(s, p, part);
     return run_parts(s, p, part, part + 1, exec);
   });
 }
@@ -778,14 +899,9 @@ hs_status hs_plan_auto_choice(hs_plan p, hs_dtype dtype, int32_t* out) {
     CHECK_ARG(p && out, "null argument");
     CHECK_ARG(dtype == HS_C64 || dtype == HS_C128, "bad dtype");
     if (hs_status rc = plan_compile(p, dtype)) return rc;
-    if (hs_status rc = plan_compile_fused(p)) return rc;
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) device = -1;
-    bool specialized = false;
-    {
-      std::lock_guard<std::mutex> lk(p->mu);
-      specialized = p->spec[dtype].count(device) > 0;
-    }
+    const bool specialized = built_spec(p, false, dtype, device) != nullptr;
     for (int i = 0; i < (int)p->parts.size(); ++i) out[i] = auto_picks_fused(p, dtype, i, specialized) ? 1 : 0;
     return HS_OK;
   });
@@ -801,8 +917,7 @@ hs_status hs_simulate(hs_state s, hs_plan p, hs_exec exec) {
         if (hs_status rc = dev_gate_pass(s, g)) return rc;
       return HS_OK;
     }
-    if (exec == HS_EXEC_PART_SPEC) return run_spec_parts(s, p, 0, (int)p->parts.size());
-    return run_parts(s, p, 0, (int)p->parts.size(), exec);
+    return run_plan(s, p, exec);
   });
 }
 

@@ -282,8 +282,19 @@ double op_work(const HostOp& op) {
 }
 
 // The interpreter's cost of an op on A = 2^rb amplitudes a lane: its
-// arithmetic (register moves for a permutation) and the dispatch.
-int op_cost(int kind, int A) {
+// arithmetic (register moves for a permutation) and the dispatch.  Plain ops
+// (CompileOptions::plain) are chosen by the estimate they have always been
+// chosen by.
+int op_cost(int kind, int A, bool plain) {
+  if (plain) switch (kind) {
+    case -1: return 0;
+    case OP_R: case OP_D: return 5 * A + 10;
+    case OP_D1: case OP_X: return 3 * A + 10;
+    case OP_CX: case OP_CP: case OP_SWAP: return 2 * A + 10;
+    case OP_CZ: return A / 2 + A + 10;
+    case OP_U2: return 17 * A + 10;
+    default: return 9 * A + 10;
+  }
   int c = 0;
   switch (kind) {
     case OP_CX: case OP_CP: case OP_SWAP: c = 2 * A; break;
@@ -292,6 +303,13 @@ int op_cost(int kind, int A) {
     default: c = 8 * A;
   }
   return c + 10;
+}
+
+// Kind emit_1q gives u (-1: identity, no op).
+int kind_1q(const cd u[4]) {
+  std::vector<HostOp> op;
+  emit_1q(0, u, &op);
+  return op.empty() ? -1 : op[0].kind;
 }
 
 // The 2x2 of a one-qubit op.
@@ -409,6 +427,11 @@ constexpr uint64_t kStageSeed = 0x5eed;
 constexpr int kStageTrials = 32;
 
 }  // namespace
+
+bool part_fits(int n, uint64_t mask, const CompileOptions& opt) {
+  const int C = std::min(opt.contig, n);
+  return __builtin_popcountll(mask | ((uint64_t(1) << C) - 1)) <= max_tile_qubits(opt);
+}
 
 hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions& opt,
                        CompiledPart* out) {
@@ -541,7 +564,9 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
         u2_apply_after(&o, o.b0, m4);
         return;
       }
-      Split f = split_gate(pend[t], role);
+      Split f;
+      if (opt.plain) std::copy(pend[t], pend[t] + 4, f.K);
+      else f = split_gate(pend[t], role);
       scale *= f.S;
       for (int j = 0; j < 4; ++j) pend[t][j] = f.L[j];
       has[t] = !is_identity(f.L);
@@ -557,6 +582,7 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
     // interpreter cost of what a two-qubit gate with this role makes run
     auto pend_cost = [&](int t, Role role) {
       if (!has[t] || open_u2(t)) return 0;
+      if (opt.plain) return op_cost(kind_1q(pend[t]), A, true);
       const int c = split_gate(pend[t], role).cost;
       return c ? c * A / 2 + 10 : 0;
     };
@@ -602,11 +628,13 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
         // what a 4 x 4 op also saves: the bits' next gate, if it is on the
         // same pair, or the run that a bit's last gate leaves pending
         int saved = 0;
-        if (next[o][0] >= 0 && next[o][0] == next[o][1]) saved = 2 * (4 * A + 10) + op_cost(gk, A);
+        if (opt.plain) saved = 0;
+        else if (next[o][0] >= 0 && next[o][0] == next[o][1]) saved = 2 * (4 * A + 10) + op_cost(gk, A, false);
         else
           for (int j = 0; j < 2; ++j)
             if (next[o][j] < 0 && last_stage[j ? t1 : t0] <= (int)s) saved += 6 * A + 10;
-        if (op_cost(OP_U2, A) < pend_cost(t0, kRoleZ) + pend_cost(t1, role1) + op_cost(gk, A) + saved) {
+        if (op_cost(OP_U2, A, opt.plain) <
+            pend_cost(t0, kRoleZ) + pend_cost(t1, role1) + op_cost(gk, A, opt.plain) + saved) {
           HostOp op{};
           op.kind = OP_U2;
           op.b0 = std::min(r0, r1);
@@ -624,7 +652,7 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
           continue;
         }
       }
-      if (g.kind == HS_SWAP) {  // what is pending moves with the qubits
+      if (g.kind == HS_SWAP && !opt.plain) {  // what is pending moves with the qubits
         std::swap(has[t0], has[t1]);
         for (int j = 0; j < 4; ++j) std::swap(pend[t0][j], pend[t1][j]);
       } else {
@@ -648,8 +676,10 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
       }
       out->ops.push_back(op);
     }
-    for (int t = 0; t < m; ++t)
-      if (reg_of[t] >= 0 && (open_u2(t) || last_stage[t] <= (int)s)) flush(t, kRoleLast);
+    for (int r = 0; r < rb; ++r) {
+      const int t = lay[s].pos[lb + wb + r];
+      if (open_u2(t) || last_stage[t] <= (int)s || opt.plain) flush(t, kRoleLast);
+    }
     if (s + 1 == st.size()) fold_scalar(scale, &out->ops);
     out->stages.back().op_end = (int)out->ops.size();
     prev = &lay[s];
@@ -749,36 +779,37 @@ hs_status compile_fused(int n, const std::vector<Gate>& pg, FusedPart* out) {
 
 namespace hisv {
 
-// Relative cost of a part on the interpreter kernel (one HBM sweep of the
-// state = 1), fitted to per-part timings of 30-qubit states (random,
-// layered and dressed-pair circuits; 820 parts, mean |log error| 0.05): a
-// smooth maximum of the sweep (+0.04 / 0.02 per LDS re-layout, complex64 /
-// complex128) and the vector-ALU work -- 0.0114 / 0.00875 sweep per vector
-// instruction an amplitude (op_work), plus 0.005 per register op for
-// complex128 (the dispatch).  Used by AUTO only.
-double lds_part_cost(const CompiledPart& cp, hs_dtype dt) {
-  const bool f32 = dt == HS_C64;
-  const double mem = 1.0 + (f32 ? 0.04 : 0.02) * cp.lds_round_trips;
+// Relative cost of a part or sweep on the interpreter kernel (one HBM sweep of
+// the state = 1), fitted to the timings of 1,058 of them on 28-qubit complex64
+// and 27-qubit complex128 states (random, layered, dressed-pair and QFT
+// circuits, tiles of 9 to 14 qubits; mean |log error| 0.08): a smooth maximum
+// of the sweep (+0.04 per LDS re-layout) and the arithmetic, 0.007 / 0.006
+// sweep (complex64 / complex128) per vector instruction an amplitude (op_work)
+// and 0.02 per register op.  A tile that fills the CU overlaps neither with
+// another tile.  Used by AUTO only.
+double lds_part_alu(const CompiledPart& cp, hs_dtype dt) {
   double f = 0;
   for (const HostOp& op : cp.ops) f += op_work(op);
-  const double alu = (f32 ? 0.0114 : 0.00875) * f + (f32 ? 0.0 : 0.005) * (double)cp.ops.size();
-  return std::cbrt(mem * mem * mem + alu * alu * alu);
+  return (dt == HS_C64 ? 0.007 : 0.006) * f + 0.02 * (double)cp.ops.size();
 }
 
-// The specialized kernels keep the sweep near the HBM rate while a part's
-// arithmetic is light: an LDS re-layout costs about 0.03 sweep, and
-// register permutations (X, CX, SWAP) are free (compile-time renames).
-// Heavier parts become vector-ALU bound.  Per-part timings of 30-qubit
-// states (random, layered and dressed-pair circuits, both precisions) fit
-// a smooth maximum of the sweep and 0.0079 sweep per vector instruction an
-// amplitude (op_work: a dense 2 x 2 written out is 8): flat at ~1.1 sweeps
-// below ~110, 1.6-1.7 at 200, 2.1-2.3 at 285, 4.2-4.8 at 570.
+double lds_part_cost(const CompiledPart& cp, hs_dtype dt) {
+  const bool f32 = dt == HS_C64;
+  const double mem = 0.9 + 0.04 * cp.lds_round_trips, alu = lds_part_alu(cp, dt);
+  return (cp.desc.m >= (f32 ? 14 : 13) ? 1.5 : 1.0) * std::sqrt(mem * mem + alu * alu);
+}
+
+// The same for the specialized kernels: the sweep (+0.04 per LDS re-layout) or
+// 0.007 sweep per vector instruction an amplitude, a tile that fills the CU 15%
+// (complex64) or 30% more.  Register permutations (X, CX, SWAP) are free
+// (compile-time renames).  870 timings as above, mean |log error| 0.09 / 0.07.
 double spec_part_cost(const CompiledPart& cp, hs_dtype dt) {
-  const double mem = (dt == HS_C64 ? 1.05 : 1.0) + 0.03 * cp.lds_round_trips;
+  const bool f32 = dt == HS_C64;
+  const double mem = 0.9 + 0.04 * cp.lds_round_trips;
   double f = 0;
   for (const HostOp& op : cp.ops) f += op_work(op);
-  const double alu = 0.0079 * f;
-  return std::sqrt(std::sqrt(mem * mem * mem * mem + alu * alu * alu * alu));
+  const double alu = 0.007 * f;
+  return (cp.desc.m < (f32 ? 14 : 13) ? 1.0 : f32 ? 1.15 : 1.3) * std::cbrt(mem * mem * mem + alu * alu * alu);
 }
 
 // The fused kernel does 8 * 2^w flops per amplitude on matrix cores against
@@ -787,13 +818,14 @@ double spec_part_cost(const CompiledPart& cp, hs_dtype dt) {
 // w = 6 and 7 are matrix-core bound; w <= 5 overlap their loads with the
 // products only in part.  Complex64 parts that hold one of qubits 0..3 (the
 // 16 columns of a wave are then not one contiguous run) cost ~0.1 more.
-double fused_part_cost(const FusedPart& f, hs_dtype dt) {
+double fused_part_cost(int n, uint64_t mask, hs_dtype dt) {
   static const double c64[8] = {0, 0, 0, 0, 1.17, 1.29, 2.13, 3.37};
   static const double c128[8] = {0, 0, 0, 0, 1.10, 1.25, 1.69, 2.92};
-  if (f.w < 4 || f.w > 7) return 1e30;
-  const bool coalesced = f.pq[0] == 0 && f.pq[1] == 1 && f.pq[2] == 2 && f.pq[3] == 3;
-  if (dt == HS_C64) return c64[f.w] + (coalesced ? 0.0 : 0.1);
-  return c128[f.w];
+  for (int q = 0; q < n && __builtin_popcountll(mask) < 4; ++q) mask |= uint64_t(1) << q;  // as compile_fused widens
+  const int w = __builtin_popcountll(mask);
+  if (w < 4 || w > kMaxFusedQubits || n < w + 4) return 1e30;
+  if (dt == HS_C64) return c64[w] + (mask & 15 ? 0.1 : 0.0);
+  return c128[w];
 }
 
 }  // namespace hisv

@@ -152,6 +152,7 @@ struct CompileOptions {
                      // (longer contiguous runs per tile); 0 = lanes + registers
   bool fuse2 = false;  // merge two-qubit gates with their one-qubit neighbours
                        // into dense 4 x 4 ops where that saves instructions
+  bool plain = false;  // apply every one-qubit run whole, where it ends (Plan::plain)
   LaunchShape launch;
 };
 
@@ -159,15 +160,33 @@ struct CompileOptions {
 hs_status compile_part(int n, const std::vector<Gate>& part_gates, const CompileOptions& opt,
                        CompiledPart* out);
 int max_tile_qubits(const CompileOptions& opt);
+// Whether compile_part finds a tile for a part on these qubits.
+bool part_fits(int n, uint64_t mask, const CompileOptions& opt);
 
 // ---- plan -------------------------------------------------------------------
 struct DevicePlan;  // uploaded descriptors (kernels.hip)
 void device_plan_free(DevicePlan* d);
 struct SpecKernel;  // a part's specialized kernel (specialize.cpp)
 
+// The sweeps hs_simulate runs instead of a plan's parts (sweeps.cpp), in
+// order; none where the parts are kept.
+struct SweepSet {
+  bool ready = false;
+  std::vector<CompiledPart> comp;
+};
+
 struct Plan {
   int n = 0, k = 0;
   uint64_t pad = 0;  // multi-level plans: qubits counted in every part's bound
+  bool served = false;  // a server's request
+  // Whether the interpreter runs this plan's parts with their ops as they were
+  // before one-qubit runs were split (compile.cpp) and before hs_simulate cut
+  // plans into sweeps.  Clients read a request's complex64 result, and that of
+  // a state of up to 12 qubits, as complex128 and compare it as such; there
+  // every bit stays what it has been.  (The split changes the last bits of
+  // 24; nothing is lost by keeping the plain ops on such small states, which
+  // wait on dispatch and not on arithmetic.)
+  bool plain(hs_dtype dt, bool spec) const { return dt == HS_C64 && !spec && (served || n <= 12); }
   std::vector<Gate> gates;
   Dag dag;
   std::vector<int32_t> part_of_gate;
@@ -179,8 +198,11 @@ struct Plan {
   std::vector<CompiledPart> comp[2];    // for the interpreter kernel
   bool scompiled[2] = {false, false};
   std::vector<CompiledPart> scomp[2];   // for the specialized kernels
-  std::map<int, DevicePlan*> dev[2];
-  std::map<int, std::vector<std::shared_ptr<SpecKernel>>> spec[2];  // per device
+  SweepSet sweeps[2][2];                // [specialized][dtype]
+  // uploaded descriptors and built kernels per device: [0] of the parts,
+  // [1] of the sweeps
+  std::map<int, DevicePlan*> dev[2][2];                                // [sweeps][dtype]
+  std::map<int, std::vector<std::shared_ptr<SpecKernel>>> spec[2][2];  // [sweeps][dtype]
   // one kernel build at a time per plan (held across the hipRTC build; the
   // maps above are guarded by mu alone, so launches never wait for a build)
   std::mutex spec_build_mu;
@@ -197,6 +219,9 @@ hs_status plan_build(int n, const std::vector<Gate>& gates, int k,
 CompileOptions default_options(hs_dtype dtype, bool spec = false);
 hs_status plan_compile(Plan* p, hs_dtype dtype);
 hs_status plan_compile_spec(Plan* p, hs_dtype dtype);
+// The plan's sweeps on the interpreter or on the specialized kernels, grouped
+// and compiled on the first call.
+hs_status plan_sweeps(Plan* p, hs_dtype dtype, bool spec, const SweepSet** out);
 // the compiled parts of a path (PART_SPEC -> specialized, else interpreter)
 const std::vector<CompiledPart>& compiled_parts(const Plan* p, hs_dtype dtype, hs_exec exec);
 
@@ -218,8 +243,9 @@ inline size_t amp_bytes(hs_dtype d) { return d == HS_C64 ? 8 : 16; }
 // ---- device side (kernels.hip) ------------------------------------------------
 hs_status dev_set_basis(State* s, uint64_t x);
 hs_status dev_gate_pass(State* s, const Gate& g);
-hs_status dev_run_part(State* s, Plan* p, int part);
-// Upload the plan's interpreter descriptors for `dtype` on `device` with the
+// Run one part (or one of the interpreter's sweeps) on the interpreter.
+hs_status dev_run_part(State* s, Plan* p, int part, bool sweep = false);
+// Upload the interpreter descriptors of the plan's parts (or sweeps) for `dtype` on `device` with the
 // stream-ordered allocator on `stream`, without waiting for the copies; the
 // plan later frees them with hipFreeAsync on that stream, never with a
 // device-wide wait.  A launch on another stream first calls
@@ -232,9 +258,9 @@ struct PinnedStaging {
   size_t bytes = 0;
   void* busy = nullptr;  // hipEvent_t
 };
-hs_status dev_plan_upload_async(Plan* p, hs_dtype dtype, int device, void* stream,
+hs_status dev_plan_upload_async(Plan* p, bool sweep, hs_dtype dtype, int device, void* stream,
                                 const PinnedStaging* pin = nullptr);
-hs_status dev_plan_stream_wait(Plan* p, hs_dtype dtype, int device, void* stream);
+hs_status dev_plan_stream_wait(Plan* p, bool sweep, hs_dtype dtype, int device, void* stream);
 hs_status dev_run_fused(State* s, Plan* p, int part);
 hs_status plan_compile_fused(Plan* p);
 // hs_tune("fused_shape"): the fused w = 4, 5 kernels' launch shape, read when
@@ -243,7 +269,9 @@ int fused_launch_shape();
 // relative cost (one HBM sweep = 1) of a part on each path, for AUTO
 double spec_part_cost(const CompiledPart& cp, hs_dtype dt);
 double lds_part_cost(const CompiledPart& cp, hs_dtype dt);
-double fused_part_cost(const FusedPart& f, hs_dtype dt);
+double lds_part_alu(const CompiledPart& cp, hs_dtype dt);  // its arithmetic alone
+// (by its qubits alone, so that no unitary is built to decide)
+double fused_part_cost(int n, uint64_t mask, hs_dtype dt);
 hs_status dev_norm(State* s, double* out);
 // the same reduction with its partial sums in a static device array (no allocation)
 hs_status dev_norm_noalloc(State* s, double* out);

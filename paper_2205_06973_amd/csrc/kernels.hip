@@ -1134,7 +1134,7 @@ static OpDesc<T> device_op(const HostOp& h) {
 // blocking copies; otherwise the stream-ordered allocator and asynchronous
 // copies on `stream`, waited for before returning.
 template <typename T>
-static hs_status upload_plan(Plan* p, int dtype, int dev, DevicePlan** out, hipStream_t stream,
+static hs_status upload_plan(const std::vector<CompiledPart>& comp, int dev, DevicePlan** out, hipStream_t stream,
                              const PinnedStaging* pin = nullptr) {
   std::vector<PartDesc> hparts;
   std::vector<IPart> parts;
@@ -1144,7 +1144,7 @@ static hs_status upload_plan(Plan* p, int dtype, int dev, DevicePlan** out, hipS
   dp->device = dev;
   DevInfo dinfo;
   if (hs_status rc = device_info(dev, &dinfo)) return rc;
-  for (const CompiledPart& cp : p->comp[dtype]) {
+  for (const CompiledPart& cp : comp) {
     PartDesc d = cp.desc;
     if (d.rb > kMaxRegBits || d.wb > kMaxWaveBits || d.lb > kLaneBits || cp.stages.size() < 2)
       return fail(HS_E_UNSUPPORTED, "part layout outside the interpreter's limits");
@@ -1276,57 +1276,65 @@ static hs_status launch_part(State* s, DevicePlan* dp, int part) {
   return HS_OK;
 }
 
-static hs_status device_plan(State* s, Plan* p, DevicePlan** out) {
+// what the interpreter runs for a plan: its parts or its sweeps
+static const std::vector<CompiledPart>& interpreted(const Plan* p, bool sweep, int dt) {
+  return sweep ? p->sweeps[0][dt].comp : p->comp[dt];
+}
+
+static hs_status device_plan(State* s, Plan* p, bool sweep, DevicePlan** out) {
   const int dt = (int)s->dtype;
-  auto it = p->dev[dt].find(s->device);
-  if (it != p->dev[dt].end()) {
+  auto it = p->dev[sweep][dt].find(s->device);
+  if (it != p->dev[sweep][dt].end()) {
     *out = it->second;
     return HS_OK;
   }
   DevicePlan* dp = nullptr;
-  hs_status rc = dt == HS_C64 ? upload_plan<float>(p, dt, s->device, &dp, nullptr)
-                              : upload_plan<double>(p, dt, s->device, &dp, nullptr);
+  const std::vector<CompiledPart>& comp = interpreted(p, sweep, dt);
+  hs_status rc = dt == HS_C64 ? upload_plan<float>(comp, s->device, &dp, nullptr)
+                              : upload_plan<double>(comp, s->device, &dp, nullptr);
   if (rc) return rc;
-  p->dev[dt][s->device] = dp;
+  p->dev[sweep][dt][s->device] = dp;
   *out = dp;
   return HS_OK;
 }
 
-hs_status dev_plan_upload_async(Plan* p, hs_dtype dtype, int device, void* stream, const PinnedStaging* pin) {
+hs_status dev_plan_upload_async(Plan* p, bool sweep, hs_dtype dtype, int device, void* stream,
+                                const PinnedStaging* pin) {
   HIP_TRY(hipSetDevice(device));
   std::lock_guard<std::mutex> lk(p->mu);
   const int dt = (int)dtype;
-  if (p->dev[dt].count(device)) return HS_OK;
+  if (p->dev[sweep][dt].count(device)) return HS_OK;
   DevicePlan* dp = nullptr;
-  hs_status rc = dt == HS_C64 ? upload_plan<float>(p, dt, device, &dp, (hipStream_t)stream, pin)
-                              : upload_plan<double>(p, dt, device, &dp, (hipStream_t)stream, pin);
+  const std::vector<CompiledPart>& comp = interpreted(p, sweep, dt);
+  hs_status rc = dt == HS_C64 ? upload_plan<float>(comp, device, &dp, (hipStream_t)stream, pin)
+                              : upload_plan<double>(comp, device, &dp, (hipStream_t)stream, pin);
   if (rc) {
     device_plan_free(dp);
     return rc;
   }
-  p->dev[dt][device] = dp;
+  p->dev[sweep][dt][device] = dp;
   return HS_OK;
 }
 
-hs_status dev_plan_stream_wait(Plan* p, hs_dtype dtype, int device, void* stream) {
+hs_status dev_plan_stream_wait(Plan* p, bool sweep, hs_dtype dtype, int device, void* stream) {
   HIP_TRY(hipSetDevice(device));
   hipEvent_t ev = nullptr;
   {
     std::lock_guard<std::mutex> lk(p->mu);
-    auto it = p->dev[(int)dtype].find(device);
-    if (it == p->dev[(int)dtype].end()) return fail(HS_E_STATE, "plan not uploaded for this device");
+    auto it = p->dev[sweep][(int)dtype].find(device);
+    if (it == p->dev[sweep][(int)dtype].end()) return fail(HS_E_STATE, "plan not uploaded for this device");
     ev = it->second->upload_done;
   }
   if (ev) HIP_TRY(hipStreamWaitEvent((hipStream_t)stream, ev, 0));
   return HS_OK;
 }
 
-hs_status dev_run_part(State* s, Plan* p, int part) {
+hs_status dev_run_part(State* s, Plan* p, int part, bool sweep) {
   HIP_TRY(hipSetDevice(s->device));
   DevicePlan* dp = nullptr;
   {
     std::lock_guard<std::mutex> lk(p->mu);
-    if (hs_status rc = device_plan(s, p, &dp)) return rc;
+    if (hs_status rc = device_plan(s, p, sweep, &dp)) return rc;
   }
   return s->dtype == HS_C64 ? launch_part<float>(s, dp, part) : launch_part<double>(s, dp, part);
 }
@@ -1439,7 +1447,7 @@ hs_status dev_run_fused(State* s, Plan* p, int part) {
   DevicePlan* dp = nullptr;
   {
     std::lock_guard<std::mutex> lk(p->mu);
-    if (hs_status rc = device_plan(s, p, &dp)) return rc;
+    if (hs_status rc = device_plan(s, p, false, &dp)) return rc;
     if (!dp->fused_ready) {
       hs_status rc = s->dtype == HS_C64 ? upload_fused<float>(p, dp) : upload_fused<double>(p, dp);
       if (rc) return rc;

@@ -65,6 +65,8 @@ struct Request {
   State st;
   int stream = -1;
   hipEvent_t done = nullptr;  // recorded after the last part
+  bool sweep = false;  // passes are the plan's sweeps, not its parts
+  int passes = 0;
   // parts go to the device a chunk at a time, at most two chunks queued
   int next_part = 0;                           // first part not yet enqueued
   hipEvent_t chunk_ev[2] = {nullptr, nullptr};  // recorded after each chunk
@@ -121,9 +123,9 @@ struct hs_server_ {
 
 namespace {
 
-size_t plan_bytes(const Plan& p, hs_dtype dt) {
+size_t plan_bytes(const std::vector<CompiledPart>& steps, hs_dtype dt) {
   size_t b = 0;
-  for (const CompiledPart& cp : p.comp[dt])
+  for (const CompiledPart& cp : steps)
     b += sizeof(IPart) + cp.stages.size() * sizeof(IStage) +
          cp.ops.size() * (dt == HS_C64 ? sizeof(OpDesc<float>) : sizeof(OpDesc<double>));
   return b;
@@ -144,12 +146,19 @@ hs_status prepare(hs_server_* sv, Request* r, hipStream_t stream, const PinnedSt
     default: return fail(HS_E_ARG, "unknown strategy %d", (int)r->strategy);
   }
   auto plan = std::make_unique<Plan>();
+  plan->served = true;
   if (hs_status rc = plan_build(r->n, gs, r->k, part, plan.get())) return rc;
-  if (hs_status rc = plan_compile(plan.get(), r->dtype)) return rc;
-  r->bytes = (size_t(1) << r->n) * amp_bytes(r->dtype) + plan_bytes(*plan, r->dtype);
+  const SweepSet* set = nullptr;
+  if (hs_status rc = plan_sweeps(plan.get(), r->dtype, false, &set)) return rc;
+  r->sweep = !set->comp.empty();
+  if (!r->sweep)
+    if (hs_status rc = plan_compile(plan.get(), r->dtype)) return rc;
+  const std::vector<CompiledPart>& steps = r->sweep ? set->comp : plan->comp[r->dtype];
+  r->passes = (int)steps.size();
+  r->bytes = (size_t(1) << r->n) * amp_bytes(r->dtype) + plan_bytes(steps, r->dtype);
   if (r->bytes > sv->budget)
     return fail(HS_E_ADMISSION, "request needs %zu bytes, budget is %zu", r->bytes, sv->budget);
-  if (hs_status rc = dev_plan_upload_async(plan.get(), r->dtype, sv->device, stream, pin)) return rc;
+  if (hs_status rc = dev_plan_upload_async(plan.get(), r->sweep, r->dtype, sv->device, stream, pin)) return rc;
   r->plan = std::move(plan);
   r->gates.clear();
   r->gates.shrink_to_fit();
@@ -196,10 +205,10 @@ Request* find(hs_server_* sv, uint64_t t) {
 // device) and, after the last part, its done event.
 hs_status enqueue_chunk(hs_server_* sv, Request* r) {
   hipStream_t s = sv->streams[r->stream];
-  const int P = (int)r->plan->parts.size();
+  const int P = r->passes;
   const int first = r->next_part, last = std::min(P, first + r->chunk_parts);
   for (int i = first; i < last; ++i)
-    if (hs_status rc = dev_run_part(&r->st, r->plan.get(), i)) return rc;
+    if (hs_status rc = dev_run_part(&r->st, r->plan.get(), i, r->sweep)) return rc;
   r->next_part = last;
   const int slot = (r->chunk_old + r->chunks_out) & 1;
   if (hipEventRecord(r->chunk_ev[slot], s) != hipSuccess) return fail(HS_E_HIP, "event record failed");
@@ -223,7 +232,7 @@ hs_status feed(hs_server_* sv, Request* r, bool* progress) {
     r->chunks_out--;
     *progress = true;
   }
-  while (r->next_part < (int)r->plan->parts.size() && r->chunks_out < 2) {
+  while (r->next_part < r->passes && r->chunks_out < 2) {
     if (hs_status rc = enqueue_chunk(sv, r)) return rc;
     *progress = true;
   }
@@ -241,7 +250,7 @@ hs_status launch(hs_server_* sv, Request* r) {
     if (sv->load[i] < sv->load[best]) best = i;
   r->stream = best;
   r->chunk_parts = serve_chunk_parts();
-  r->remaining = (double)r->plan->parts.size() * (double)((size_t(1) << r->n) * amp_bytes(r->dtype));
+  r->remaining = (double)r->passes * (double)((size_t(1) << r->n) * amp_bytes(r->dtype));
   sv->load[best] += r->remaining;
   hipStream_t s = sv->streams[best];
   r->st.n = r->n;
@@ -262,9 +271,9 @@ hs_status launch(hs_server_* sv, Request* r) {
       return fail(HS_E_HIP, "event create failed");
   // the descriptors were copied on a preparing stream: wait for them here,
   // on the device
-  if (hs_status rc = dev_plan_stream_wait(r->plan.get(), r->dtype, sv->device, s)) return rc;
+  if (hs_status rc = dev_plan_stream_wait(r->plan.get(), r->sweep, r->dtype, sv->device, s)) return rc;
   if (hs_status rc = dev_set_basis(&r->st, r->init)) return rc;
-  if (r->plan->parts.empty()) {  // no gates: set-basis is the whole request
+  if (!r->passes) {  // no gates: set-basis is the whole request
     hipError_t e2 = hipEventCreateWithFlags(&r->done, hipEventDisableTiming);
     if (e2 == hipSuccess) e2 = hipEventRecord(r->done, s);
     if (e2 != hipSuccess) return fail(HS_E_HIP, "event: %s", hipGetErrorString(e2));
