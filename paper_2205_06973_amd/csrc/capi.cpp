@@ -29,6 +29,9 @@ Plan::~Plan() {
   for (auto& of : dev)
     for (auto& by_device : of)
       for (auto& kv : by_device) device_plan_free(kv.second);
+  for (auto& of : fdev)
+    for (auto& by_device : of)
+      for (auto& kv : by_device) device_fused_free(kv.second);
 }
 
 // Tunable knobs (hs_tune), read when a plan is compiled.  Register bits per
@@ -792,6 +795,7 @@ static hs_status run_spec_part(hs_state s, Plan* p, int part) {
 // AUTO: the plan's sweeps (`set`) or its parts, and on `ks` if they are
 // specialized kernels.  Only PART_SPEC builds kernels here.
 struct WholePlan {
+  const FusedSet* fused = nullptr;  // the plan's gates as dense unitaries
   const SweepSet* set = nullptr;
   const std::vector<std::shared_ptr<SpecKernel>>* ks = nullptr;
   bool sweep = false;
@@ -799,6 +803,11 @@ struct WholePlan {
 static hs_status choose_whole(Plan* p, hs_dtype dt, int device, hs_exec exec, bool build, WholePlan* w) {
   const bool spec = exec == HS_EXEC_PART_SPEC;
   w->ks = exec == HS_EXEC_AUTO ? built_spec(p, true, dt, device) : nullptr;
+  if (exec == HS_EXEC_PART_FUSED || exec == HS_EXEC_AUTO) {
+    if (hs_status rc = plan_fused_set(p, dt, false, &w->fused)) return rc;
+    if (w->fused->gates.empty()) w->fused = nullptr;
+    if (exec == HS_EXEC_PART_FUSED) return HS_OK;
+  }
   double parts = 0;  // AUTO: the parts, each on its cheaper kernel
   if (exec == HS_EXEC_AUTO) {
     if (hs_status rc = plan_compile(p, dt)) return rc;
@@ -808,6 +817,8 @@ static hs_status choose_whole(Plan* p, hs_dtype dt, int device, hs_exec exec, bo
       parts += std::min(fused_cost(p, dt, i), gate_cost(p, dt, i, parts_built));
       alu += lds_part_alu(p->comp[dt][i], dt);
     }
+    if (w->fused && w->fused->cost < parts) parts = w->fused->cost;
+    else w->fused = nullptr;
     // the interpreter's arithmetic hardly changes with the cut (the sweeps
     // save up to a tenth): where it alone costs more, nothing is regrouped
     if (!w->ks && 0.9 * alu > parts) return HS_OK;
@@ -823,16 +834,23 @@ static hs_status choose_whole(Plan* p, hs_dtype dt, int device, hs_exec exec, bo
     double sweeps = 0;
     for (const CompiledPart& cp : w->set->comp) sweeps += w->ks ? spec_part_cost(cp, dt) : lds_part_cost(cp, dt);
     w->sweep = sweeps <= parts;
+    if (w->sweep) w->fused = nullptr;
   }
   return HS_OK;
 }
 
 static hs_status run_plan(hs_state s, Plan* p, hs_exec exec) {
   const int P = (int)p->parts.size();
-  if (exec == HS_EXEC_PART_FUSED) return run_parts(s, p, 0, P, exec);
   if (hipSetDevice(s->device) != hipSuccess) return fail(HS_E_HIP, "hipSetDevice failed");
   WholePlan w;
   if (hs_status rc = choose_whole(p, s->dtype, s->device, exec, true, &w)) return rc;
+  if (w.fused) {
+    if (hs_status rc = plan_fused_set(p, s->dtype, true, &w.fused)) return rc;
+    for (int i = 0; i < (int)w.fused->parts.size(); ++i)
+      if (hs_status rc = dev_run_fused(s, p, i, true)) return rc;
+    return HS_OK;
+  }
+  if (exec == HS_EXEC_PART_FUSED) return run_parts(s, p, 0, P, exec);
   if (exec == HS_EXEC_PART_SPEC || (w.sweep && w.ks)) return launch_spec(s, p, w.sweep, *w.ks, 0, (int)w.ks->size());
   if (!w.sweep) return run_parts(s, p, 0, P, exec);
   for (int i = 0; i < (int)w.set->comp.size(); ++i)
@@ -845,15 +863,15 @@ hs_status hs_plan_num_sweeps(hs_plan p, hs_dtype dtype, hs_exec exec, int* out) 
     CHECK_ARG(p && out, "null argument");
     CHECK_ARG(dtype == HS_C64 || dtype == HS_C128, "bad dtype %d", (int)dtype);
     if (hs_status rc = check_exec(exec)) return rc;
-    if (exec == HS_EXEC_GATE_PER_PASS || exec == HS_EXEC_PART_FUSED) {
-      *out = (int)(exec == HS_EXEC_PART_FUSED ? p->parts.size() : p->gates.size());
+    if (exec == HS_EXEC_GATE_PER_PASS) {
+      *out = (int)p->gates.size();
       return HS_OK;
     }
     int device = 0;
     if (hipGetDevice(&device) != hipSuccess) device = -1;
     WholePlan w;
     if (hs_status rc = choose_whole(p, dtype, device, exec, false, &w)) return rc;
-    *out = (int)(w.sweep ? w.set->comp.size() : p->parts.size());
+    *out = (int)(w.fused ? w.fused->gates.size() : w.sweep ? w.set->comp.size() : p->parts.size());
     return HS_OK;
   });
 }

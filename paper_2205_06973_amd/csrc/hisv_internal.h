@@ -130,7 +130,7 @@ struct CompiledPart {
 // U acts on the qubits sq[0..w) (bit b of a row/column index = qubit sq[b]),
 // columns of the batched product are the settings of the 4 column qubits.
 struct FusedPart {
-  int w = 0;                  // 4 or 5
+  int w = 0;                  // 4 to 7
   int m = 0;                  // tile = w + 4 qubits
   uint64_t tiles = 0;         // 2^(n - m)
   int8_t sq[8] = {0};
@@ -175,6 +175,18 @@ struct SweepSet {
   std::vector<CompiledPart> comp;
 };
 
+// The pieces hs_simulate applies as dense unitaries instead of a plan's parts
+// (sweeps.cpp), in order; none where the parts are the cheaper.
+struct FusedSet {
+  bool ready = false, built = false;
+  double cost = 0;                       // in HBM sweeps
+  std::vector<std::vector<Gate>> gates;  // of each piece
+  std::vector<FusedPart> parts;          // built on first use
+};
+
+struct DeviceFused;  // uploaded unitaries (kernels.hip)
+void device_fused_free(DeviceFused* d);
+
 struct Plan {
   int n = 0, k = 0;
   uint64_t pad = 0;  // multi-level plans: qubits counted in every part's bound
@@ -211,6 +223,8 @@ struct Plan {
   std::string spec_async_msg[2];
   bool fused_built = false;
   std::vector<FusedPart> fused;  // w = 0 where a part has no fused form
+  FusedSet fused_set[2];         // [dtype]
+  std::map<int, DeviceFused*> fdev[2][2];  // per device, [0] of the parts, [1] of the set; [dtype]
   ~Plan();
 };
 
@@ -261,8 +275,11 @@ struct PinnedStaging {
 hs_status dev_plan_upload_async(Plan* p, bool sweep, hs_dtype dtype, int device, void* stream,
                                 const PinnedStaging* pin = nullptr);
 hs_status dev_plan_stream_wait(Plan* p, bool sweep, hs_dtype dtype, int device, void* stream);
-hs_status dev_run_fused(State* s, Plan* p, int part);
+// Apply a part (or a piece of the plan's fused set) as its dense unitary.
+hs_status dev_run_fused(State* s, Plan* p, int part, bool of_set = false);
 hs_status plan_compile_fused(Plan* p);
+// The plan's gates cut anew for the fused kernels; `build` makes the unitaries.
+hs_status plan_fused_set(Plan* p, hs_dtype dtype, bool build, const FusedSet** out);
 // hs_tune("fused_shape"): the fused w = 4, 5 kernels' launch shape, read when
 // a plan's fused descriptors are uploaded
 int fused_launch_shape();

@@ -472,7 +472,7 @@ part_pass_kernel(cplx<T>* __restrict__ st, const IPart* __restrict__ pd,
 // ---------------------------------------------------------------------------
 // fused part-pass kernel: one dense unitary per part on matrix cores
 // ---------------------------------------------------------------------------
-// For a part on w qubits (w = 4 or 5) every outer setting is a column of X
+// For a part on w qubits (w = 4 to 7) every outer setting is a column of X
 // (2^w rows, one per setting of the part's qubits); Y = U X for all columns.
 // A wavefront takes 16 columns at a time -- the settings of the 4 lowest
 // other qubits, so column runs are contiguous -- and computes the complex
@@ -514,15 +514,9 @@ __device__ __forceinline__ uint64_t deposit(uint32_t v, const int8_t* q, int cou
 // U arrives in fragment order: fragment f = rb * (2^w / 4) + ks holds, in lane
 // l, U[16 rb + l % 16][4 ks + l / 16]; the real parts of all fragments come
 // first, then the imaginary parts.  For w <= 5 a wave keeps all of U in
-// registers (complex128 at w = 5 excepted); wider U (64x64, 128x128) is read
+// registers (complex128 at w = 5 excepted); wider U (complex128 w = 7) is read
 // fragment by fragment from the L2-resident copy -- one contiguous wave load
-// per fragment.  In
-// FP32 a wave then takes two tiles (32 columns) so that each fragment feeds
-// eight matrix-core products, halving the L2 traffic for U.
-template <typename T, int W>
-constexpr int fused_tiles_per_wave() {
-  return (W >= 6 && sizeof(T) == 4) ? 2 : 1;
-}
+// per fragment.
 
 template <typename T, int W, bool PIPE>
 __global__ void __launch_bounds__(256)
@@ -537,7 +531,6 @@ fused_pass_kernel(cplx<T>* __restrict__ st, const FusedDesc* __restrict__ fd, co
   // one wave per SIMD), which reads U from the L1/L2-resident copy instead
   constexpr bool kRegU = W <= 4 || (W == 5 && sizeof(T) == 4);
   constexpr bool kPipe = PIPE && W <= 5;  // software-pipelined (see below)
-  constexpr int CG = fused_tiles_per_wave<T, W>();
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t i16 = lane & 15, g4 = lane >> 4;
   const int m = fd->m;
@@ -600,10 +593,10 @@ fused_pass_kernel(cplx<T>* __restrict__ st, const FusedDesc* __restrict__ fd, co
   uint64_t row_ld[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) row_ld[ks] = dep(4 * ks, 0, W);
-  // a workgroup's 4 waves take 4 * CG consecutive tiles; with xcd set (grid
+  // a workgroup's 4 waves take 4 consecutive tiles; with xcd set (grid
   // and group count multiples of 8) XCD x = blockIdx % 8 sweeps a contiguous
   // run
-  const uint64_t groups = (tiles + 4 * CG - 1) / (4 * CG);
+  const uint64_t groups = (tiles + 3) / 4;
   uint64_t g = blockIdx.x, step = gridDim.x, end = groups;
   if (xcd) {
     const uint64_t per = groups >> 3;
@@ -614,8 +607,8 @@ fused_pass_kernel(cplx<T>* __restrict__ st, const FusedDesc* __restrict__ fd, co
   }
   // wave-uniform: tile indices, bases and the valid flags stay in scalar
   // registers (address arithmetic on the SALU, stores under a scalar branch)
-  const uint64_t wave_tile = (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * CG;
-  // X of this wave's tiles in group gg (zero columns past the last tile)
+  const uint64_t wave_tile = (uint64_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // X of this wave's tile in group gg
   // (branch-free: a wave past the last tile reads tile 0 and discards its
   // products, so no load sits in a conditional block or feeds a select --
   // either would make the wave wait for the load right away)
@@ -623,32 +616,23 @@ fused_pass_kernel(cplx<T>* __restrict__ st, const FusedDesc* __restrict__ fd, co
   // at or above log2(tiles) is set -- a 64-bit test the scalar unit has (it
   // has no 64-bit ordered compare)
   const uint64_t past = ~(tiles - 1);
-  auto load = [&](uint64_t gg, T (&xr)[CG][KS], T (&xi)[CG][KS], uint64_t (&base)[CG], bool (&valid)[CG]) {
-    const uint64_t tile0 = gg * 4 * CG + wave_tile;
+  auto load = [&](uint64_t gg, T (&xr)[KS], T (&xi)[KS], uint64_t& base, bool& valid) {
+    const uint64_t tile = gg * 4 + wave_tile;
+    valid = (tile & past) == 0;
+    base = base_of(valid ? tile : 0);
 #pragma unroll
-    for (int c = 0; c < CG; ++c) {
-      valid[c] = ((tile0 + c) & past) == 0;
-      base[c] = base_of(valid[c] ? tile0 + c : 0);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const cplx<T> v = st[base[c] + row_ld[ks] + lane_ld];
-        xr[c][ks] = v.x;
-        xi[c][ks] = v.y;
-      }
+    for (int ks = 0; ks < KS; ++ks) {
+      const cplx<T> v = st[base + row_ld[ks] + lane_ld];
+      xr[ks] = v.x;
+      xi[ks] = v.y;
     }
   };
   // Y = U X on the matrix cores, stored in place
-  auto product = [&](const T (&xr)[CG][KS], const T (&xi)[CG][KS], const uint64_t (&base)[CG],
-                     const bool (&valid)[CG]) {
+  auto product = [&](const T (&xr)[KS], const T (&xi)[KS], uint64_t base, bool valid) {
     constexpr int kRbUnroll = kRegU ? RBK : 1;
 #pragma unroll kRbUnroll
     for (int rb = 0; rb < RBK; ++rb) {
-      v4 yr[CG], yi[CG];
-#pragma unroll
-      for (int c = 0; c < CG; ++c) {
-        yr[c] = v4{0, 0, 0, 0};
-        yi[c] = v4{0, 0, 0, 0};
-      }
+      v4 yr = v4{0, 0, 0, 0}, yi = v4{0, 0, 0, 0};
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         T ar, ai, nai;
@@ -662,30 +646,25 @@ fused_pass_kernel(cplx<T>* __restrict__ st, const FusedDesc* __restrict__ fd, co
           ai = Ui[f * 64 + lane];
           nai = -ai;
         }
-#pragma unroll
-        for (int c = 0; c < CG; ++c) {
-          yr[c] = Mfma<T>::mma(ar, xr[c][ks], yr[c]);
-          yr[c] = Mfma<T>::mma(nai, xi[c][ks], yr[c]);
-          yi[c] = Mfma<T>::mma(ar, xi[c][ks], yi[c]);
-          yi[c] = Mfma<T>::mma(ai, xr[c][ks], yi[c]);
-        }
+        yr = Mfma<T>::mma(ar, xr[ks], yr);
+        yr = Mfma<T>::mma(nai, xi[ks], yr);
+        yi = Mfma<T>::mma(ar, xi[ks], yi);
+        yi = Mfma<T>::mma(ai, xr[ks], yi);
       }
-#pragma unroll
-      for (int c = 0; c < CG; ++c) {
-        if (!valid[c]) continue;
+      if (valid) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           cplx<T> o;
-          o.x = yr[c][v];
-          o.y = yi[c][v];
-          st[base[c] + dep(16 * rb + (f64 ? 4 * v : v), 0, W) + lane_st] = o;
+          o.x = yr[v];
+          o.y = yi[v];
+          st[base + dep(16 * rb + (f64 ? 4 * v : v), 0, W) + lane_st] = o;
         }
       }
     }
   };
-  T xr[CG][KS], xi[CG][KS];
-  uint64_t base[CG];
-  bool valid[CG];
+  T xr[KS], xi[KS];
+  uint64_t base;
+  bool valid;
   if (kPipe) {
     // w <= 5: a persistent grid, software-pipelined per wave -- the next
     // group's loads are issued before this group's products, so each wave
@@ -694,9 +673,9 @@ fused_pass_kernel(cplx<T>* __restrict__ st, const FusedDesc* __restrict__ fd, co
     // Two register sets alternate (no copies between iterations, which
     // would wait for the loads), and the loads are unconditional: past the
     // end a wave re-reads its current group, whose products it discards.
-    T yr2[CG][KS], yi2[CG][KS];
-    uint64_t base2[CG];
-    bool valid2[CG];
+    T yr2[KS], yi2[KS];
+    uint64_t base2;
+    bool valid2;
     if (g < end) load(g, xr, xi, base, valid);
     while (g < end) {
       const uint64_t g1 = g + step;
@@ -713,6 +692,148 @@ fused_pass_kernel(cplx<T>* __restrict__ st, const FusedDesc* __restrict__ fd, co
       load(g, xr, xi, base, valid);
       product(xr, xi, base, valid);
     }
+  }
+}
+
+// The same product with U in LDS, for widths whose U fits there beside enough
+// waves (complex64 w = 5, 6, 7: 8, 32, 128 KiB; complex128 w = 5, 6: 16, 64 KiB).
+// A persistent grid reads U once a workgroup.  The K loop is outermost: all
+// row blocks accumulate at once, so X[ks] is dead after its products and the
+// next tile's X[ks] is loaded into its registers right there.  A wave so has
+// the next tile's loads in flight under a whole tile's products, without a
+// second register set.
+template <typename T, int W>
+constexpr int fused_lds_threads() { return W == 7 ? 512 : 256; }
+
+template <typename T, int W>
+__global__ void __launch_bounds__((fused_lds_threads<T, W>()))
+fused_lds_kernel(cplx<T>* __restrict__ st, const FusedDesc* __restrict__ fd, const T* __restrict__ umat,
+                 uint32_t xcd, uint32_t chunk) {
+  using v4 = typename Mfma<T>::v4;
+  constexpr int R = 1 << W, RBK = R / 16, KS = R / 4, NF = RBK * KS;
+  constexpr int NT = fused_lds_threads<T, W>(), WAVES = NT / 64;
+  // fragment f = ks * RBK + rb: lane l's (re, im) of U[16 rb + l % 16][4 ks + l / 16]
+  __shared__ cplx<T> us[NF * 64];
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t i16 = lane & 15, g4 = lane >> 4;
+  const uint64_t tiles = fd->tiles;
+  const T* Ur = umat + fd->u_off;
+  for (int i = threadIdx.x; i < NF * 64; i += NT) {
+    const int f = i >> 6, o = ((f % RBK) * KS + f / RBK) * 64 + (i & 63);
+    us[i].x = Ur[o];
+    us[i].y = Ur[NF * 64 + o];
+  }
+  __syncthreads();
+  uint32_t qw[6];
+  {
+    const uint32_t* q32 = reinterpret_cast<const uint32_t*>(fd->sq);
+#pragma unroll
+    for (int i = 0; i < 6; ++i) qw[i] = __builtin_amdgcn_readfirstlane(q32[i]);
+  }
+  auto qb = [&](int b) -> int { return (int)(int8_t)(qw[b >> 2] >> (8 * (b & 3))); };
+  auto dep = [&](uint32_t v, int first, int count) -> uint64_t {
+    uint64_t g = 0;
+#pragma unroll
+    for (int b = 0; b < count; ++b) g |= uint64_t((v >> b) & 1u) << qb(first + b);
+    return g;
+  };
+  auto base_of = [&](uint64_t t) -> uint64_t {
+#pragma unroll
+    for (int i = 0; i < W + 4; ++i) {
+      const int q = qb(12 + i);
+      t = ((t >> q) << (q + 1)) | (t & ((uint64_t(1) << q) - 1));
+    }
+    return t;
+  };
+  constexpr bool f64 = sizeof(T) == 8;
+  const uint64_t col = dep(i16, 8, 4);
+  const uint64_t lane_ld = col + dep(g4, 0, 2);
+  const uint64_t lane_st = f64 ? lane_ld : col + dep(g4 << 2, 0, W);
+  const uint64_t groups = (tiles + WAVES - 1) / WAVES;
+  uint64_t g = (uint64_t)blockIdx.x * chunk, end = groups;
+  if (xcd) {
+    const uint64_t per = groups >> 3;
+    const uint32_t x = blockIdx.x & 7u;
+    g = x * per + (uint64_t)(blockIdx.x >> 3) * chunk;
+    end = (x + 1) * per;
+  }
+  if (g + chunk < end) end = g + chunk;
+  const uint64_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t past = ~(tiles - 1);  // tiles is a power of two
+  cplx<T>* const p_ld = st + lane_ld;
+  cplx<T>* const p_st = st + lane_st;
+  // Offsets of the row bits.  Opaque in each iteration: the sums below are
+  // then formed where they are used, on the scalar unit, instead of being
+  // kept in registers (one 64-bit value a lane for each row) over the loop.
+  uint64_t bit[W];
+#pragma unroll
+  for (int b = 0; b < W; ++b) bit[b] = uint64_t(1) << qb(b);
+  auto row = [&](int r) -> uint64_t {
+    uint64_t o = 0;
+#pragma unroll
+    for (int b = 0; b < W; ++b)
+      if (r >> b & 1) o += bit[b];
+    return o;
+  };
+  T xr[KS], xi[KS];
+  uint64_t tile = g * WAVES + wave;
+  bool valid = g < end && (tile & past) == 0;
+  uint64_t base = base_of(valid ? tile : 0);
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    const cplx<T> v = p_ld[base + row(4 * ks)];
+    xr[ks] = v.x;
+    xi[ks] = v.y;
+  }
+  cplx<T> a[RBK];
+#pragma unroll
+  for (int rb = 0; rb < RBK; ++rb) a[rb] = us[rb * 64 + lane];
+  for (; g < end; ++g) {
+#pragma unroll
+    for (int b = 0; b < W; ++b) asm volatile("" : "+s"(bit[b]));
+    // the next group's tile; past the end the wave re-reads tile 0 for nothing
+    const uint64_t gn = g + 1;
+    tile = gn * WAVES + wave;
+    const bool next_valid = gn < end && (tile & past) == 0;
+    const uint64_t next = base_of(next_valid ? tile : 0);
+    v4 yr[RBK], yi[RBK];
+#pragma unroll
+    for (int rb = 0; rb < RBK; ++rb) yr[rb] = yi[rb] = v4{0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      // U's next column of fragments, this step's products, X's refill; the
+      // barrier keeps the compiler from sinking the refills below the products
+      const T br = xr[ks], bi = xi[ks], nbi = -bi;
+      cplx<T> an[RBK];
+#pragma unroll
+      for (int rb = 0; rb < RBK; ++rb) an[rb] = us[((ks + 1) % KS * RBK + rb) * 64 + lane];
+#pragma unroll
+      for (int rb = 0; rb < RBK; ++rb) {
+        yr[rb] = Mfma<T>::mma(a[rb].x, br, yr[rb]);
+        yi[rb] = Mfma<T>::mma(a[rb].x, bi, yi[rb]);
+        yr[rb] = Mfma<T>::mma(a[rb].y, nbi, yr[rb]);
+        yi[rb] = Mfma<T>::mma(a[rb].y, br, yi[rb]);
+      }
+      const cplx<T> v = p_ld[next + row(4 * ks)];
+      xr[ks] = v.x;
+      xi[ks] = v.y;
+#pragma unroll
+      for (int rb = 0; rb < RBK; ++rb) a[rb] = an[rb];
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (valid) {
+#pragma unroll
+      for (int rb = 0; rb < RBK; ++rb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          cplx<T> o;
+          o.x = yr[rb][v];
+          o.y = yi[rb][v];
+          p_st[base + row(16 * rb + (f64 ? 4 * v : v))] = o;
+        }
+    }
+    base = next;
+    valid = next_valid;
   }
 }
 
@@ -1000,15 +1121,33 @@ struct DevicePlan {
   std::vector<int> rb;               // register bits of the kernel per part
   std::vector<unsigned> grid;        // grid per part
   std::vector<uint8_t> xcd;          // XCD-contiguous tile runs
-  // fused path (uploaded on first use)
-  bool fused_ready = false;
-  FusedDesc* fparts = nullptr;
-  void* fmat = nullptr;
-  std::vector<FusedDesc> h_fparts;
-  std::vector<unsigned> fgrid;
-  std::vector<uint8_t> fxcd;
-  std::vector<uint8_t> fpipe;  // software-pipelined kernel (persistent grid)
 };
+
+// ---- uploaded unitaries -------------------------------------------------------
+// The kernel and launch of a fused part.
+struct FusedLaunch {
+  int w = 0;
+  const void* fn = nullptr;
+  int block = 256;
+  unsigned grid = 1;
+  uint32_t xcd = 0;    // XCD-contiguous tile runs
+  uint32_t chunk = 0;  // consecutive tile groups of a workgroup (fused_lds_kernel)
+};
+
+struct DeviceFused {
+  int device = 0;
+  FusedDesc* parts = nullptr;
+  void* mat = nullptr;
+  std::vector<FusedLaunch> launch;
+};
+
+void device_fused_free(DeviceFused* d) {
+  if (!d) return;
+  (void)hipSetDevice(d->device);
+  if (d->parts) (void)hipFree(d->parts);
+  if (d->mat) (void)hipFree(d->mat);
+  delete d;
+}
 
 // Best effort: called from destructors, where an error cannot be returned.
 void device_plan_free(DevicePlan* d) {
@@ -1019,8 +1158,6 @@ void device_plan_free(DevicePlan* d) {
     if (d->async_alloc) (void)hipFreeAsync(ptr, (hipStream_t)d->free_stream);
     else (void)hipFree(ptr);
   }
-  if (d->fparts) (void)hipFree(d->fparts);
-  if (d->fmat) (void)hipFree(d->fmat);
   if (d->upload_done) (void)hipEventDestroy(d->upload_done);
   delete d;
 }
@@ -1339,11 +1476,81 @@ hs_status dev_run_part(State* s, Plan* p, int part, bool sweep) {
   return s->dtype == HS_C64 ? launch_part<float>(s, dp, part) : launch_part<double>(s, dp, part);
 }
 
+// Kernel and launch shape of a fused part on `tiles` tiles.
+//
+// w = 4 and complex128 w = 7 (U is 256 KiB) run the plain kernel, one group of
+// tiles a workgroup; w = 5 and up run fused_lds_kernel.  Its workgroups take
+// `chunk` consecutive groups.  w = 5 waits on HBM, which goes fastest when the
+// workgroups in flight cover one narrow run of memory: as few groups as pay
+// for reading U (28 qubits, sweeps of the state; complex64 chunks of 2 / 4 /
+// 16 and a persistent grid: 1.02 / 1.00 / 1.08 / 1.09; complex128 0.94 / 1.00 /
+// 1.21 / 1.06).  w = 6 and 7 wait on the matrix cores and on reading U: one
+// round of two workgroups a CU (w = 7: one, by its LDS; complex64 w = 6 chunks
+// of 4 / 16 / that: 1.47 / 1.48 / 1.38).
+//
+// hs_tune("fused_shape") asks for the kernel that keeps U in registers or reads
+// it from L2 for w = 4, 5: 0 = one group a workgroup, 1 = its software-pipelined
+// form and 2 = its plain form on a persistent grid.
 template <typename T>
-static hs_status upload_fused(Plan* p, DevicePlan* dp) {
+static hs_status fused_launch(int w, uint64_t tiles, int device, FusedLaunch* l) {
+  l->w = w;
+  if (!w) return HS_OK;
+  const int shape = w <= 5 ? fused_launch_shape() : -1;
+  const bool lds = w > 4 && shape < 0 && !(w == 7 && sizeof(T) == 8);
+  switch (w) {
+    case 4:
+      l->fn = shape == 1 ? (const void*)fused_pass_kernel<T, 4, true> : (const void*)fused_pass_kernel<T, 4, false>;
+      break;
+    case 5:
+      l->fn = lds          ? (const void*)fused_lds_kernel<T, 5>
+              : shape == 1 ? (const void*)fused_pass_kernel<T, 5, true>
+                           : (const void*)fused_pass_kernel<T, 5, false>;
+      break;
+    case 6: l->fn = (const void*)fused_lds_kernel<T, 6>; break;
+    case 7:
+      if constexpr (sizeof(T) == 4) l->fn = (const void*)fused_lds_kernel<T, 7>;
+      else l->fn = (const void*)fused_pass_kernel<T, 7, false>;
+      break;
+    default: return fail(HS_E_UNSUPPORTED, "no fused kernel for %d qubits", w);
+  }
+  DevInfo di;
+  if (hs_status rc = device_info(device, &di)) return rc;
+  if (lds) l->block = w == 7 ? fused_lds_threads<T, 7>() : fused_lds_threads<T, 6>();
+  const uint64_t per_wg = l->block / 64, groups = (tiles + per_wg - 1) / per_wg;
+  uint64_t chunk = 1, g = groups;
+  if (lds) {
+    if (w == 5) chunk = sizeof(T) == 4 ? 4 : 2;
+    else chunk = std::max<uint64_t>(1, groups / ((uint64_t)di.cus * (w == 6 ? 2 : 1)));
+    g = (groups + chunk - 1) / chunk;
+  } else if (shape > 0) {
+    int per_cu = 0;
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, l->fn, l->block, 0));
+    g = std::min<uint64_t>(groups, (uint64_t)std::max(1, per_cu) * di.cus);
+  }
+  const uint64_t most = (uint64_t(1) << 31) / l->block;
+  if (g > most && lds) {
+    chunk = (groups + most - 1) / most;
+    g = (groups + chunk - 1) / chunk;
+  }
+  g = std::max<uint64_t>(1, std::min(g, most));
+  // each XCD sweeps a contiguous eighth of the groups; with chunks, the eighth
+  // has to be whole chunks
+  if (groups % (8 * chunk) == 0 && g >= 8) {
+    g &= ~uint64_t(7);
+    l->xcd = 1;
+  }
+  l->chunk = (uint32_t)chunk;
+  l->grid = (unsigned)g;
+  return HS_OK;
+}
+
+template <typename T>
+static hs_status upload_fused(const std::vector<FusedPart>& parts, int device, DeviceFused** out) {
   std::vector<FusedDesc> fds;
   std::vector<T> mats;
-  for (const FusedPart& f : p->fused) {
+  auto dp = std::unique_ptr<DeviceFused, void (*)(DeviceFused*)>(new DeviceFused, device_fused_free);
+  dp->device = device;
+  for (const FusedPart& f : parts) {
     FusedDesc d{};
     d.w = f.w;
     d.m = f.m;
@@ -1362,98 +1569,44 @@ static hs_status upload_fused(Plan* p, DevicePlan* dp) {
             mats.push_back((T)(part_im ? z.imag() : z.real()));
           }
     fds.push_back(d);
-    // one workgroup of four wavefronts per 4 * (tiles per wave) tiles,
-    // XCD-contiguous runs
-    uint64_t per_wg = 4;
-    switch (f.w) {
-      case 6: per_wg *= fused_tiles_per_wave<T, 6>(); break;
-      case 7: per_wg *= fused_tiles_per_wave<T, 7>(); break;
-      default: break;
-    }
-    const uint64_t groups = (f.tiles + per_wg - 1) / per_wg;
-    uint64_t g = std::max<uint64_t>(1, std::min<uint64_t>(groups, (uint64_t(1) << 31) / 256));
-    // w = 4, 5: launch shape from hs_tune("fused_shape"): 0 = one tile group
-    // per workgroup; 1 = software-pipelined kernel, 2 = plain kernel, each
-    // on a persistent grid of as many workgroups as the device keeps
-    // resident (U is then read once per workgroup, not once per group).
-    // By default (-1) the measured best per width and precision: on 30-qubit
-    // states the persistent plain kernel for complex64 w = 5 (1.31 sweeps
-    // against 1.40), one group per workgroup otherwise (complex64 w = 4:
-    // 1.13-1.23 against 1.28-1.32; complex128 w = 4 / 5: 0.93-1.09 / 1.19-1.21
-    // against 1.02-1.19 / 1.22-1.27).
-    int shape = (f.w == 4 || f.w == 5) ? fused_launch_shape() : 0;
-    if (shape < 0) shape = (sizeof(T) == 4 && f.w == 5) ? 2 : 0;
-    if (shape) {
-      int per_cu = 0;
-      const void* fn = nullptr;
-      if (f.w == 4)
-        fn = shape == 1 ? (const void*)fused_pass_kernel<T, 4, true> : (const void*)fused_pass_kernel<T, 4, false>;
-      else
-        fn = shape == 1 ? (const void*)fused_pass_kernel<T, 5, true> : (const void*)fused_pass_kernel<T, 5, false>;
-      HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 256, 0));
-      DevInfo di;
-      if (hs_status rc = device_info(dp->device, &di)) return rc;
-      g = std::max<uint64_t>(1, std::min<uint64_t>(g, (uint64_t)std::max(1, per_cu) * di.cus));
-    }
-    dp->fpipe.push_back(shape == 1 ? 1 : 0);
-    uint8_t x = 0;
-    if (groups % 8 == 0 && g >= 8) {
-      g &= ~uint64_t(7);
-      x = 1;
-    }
-    dp->fgrid.push_back((unsigned)g);
-    dp->fxcd.push_back(x);
+    FusedLaunch l;
+    if (hs_status rc = fused_launch<T>(f.w, f.tiles, device, &l)) return rc;
+    dp->launch.push_back(l);
   }
   if (mats.empty()) mats.push_back(T(0));
   if (fds.empty()) fds.push_back(FusedDesc{});
-  HIP_TRY(hipMalloc(&dp->fparts, fds.size() * sizeof(FusedDesc)));
-  HIP_TRY(hipMalloc(&dp->fmat, mats.size() * sizeof(T)));
-  HIP_TRY(hipMemcpy(dp->fparts, fds.data(), fds.size() * sizeof(FusedDesc), hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpy(dp->fmat, mats.data(), mats.size() * sizeof(T), hipMemcpyHostToDevice));
-  dp->h_fparts = fds;
-  dp->fused_ready = true;
+  HIP_TRY(hipMalloc(&dp->parts, fds.size() * sizeof(FusedDesc)));
+  HIP_TRY(hipMalloc(&dp->mat, mats.size() * sizeof(T)));
+  HIP_TRY(hipMemcpy(dp->parts, fds.data(), fds.size() * sizeof(FusedDesc), hipMemcpyHostToDevice));
+  HIP_TRY(hipMemcpy(dp->mat, mats.data(), mats.size() * sizeof(T), hipMemcpyHostToDevice));
+  *out = dp.release();
   return HS_OK;
 }
 
-template <typename T>
-static hs_status launch_fused(State* s, DevicePlan* dp, int part) {
-  const FusedDesc& d = dp->h_fparts[part];
-  cplx<T>* st = (cplx<T>*)s->ptr;
-  const FusedDesc* fd = dp->fparts + part;
-  const T* um = (const T*)dp->fmat;
-  hipStream_t str = stream_of(s);
-  const dim3 grid(dp->fgrid[part]);
-  const uint32_t xcd = dp->fxcd[part];
-  const bool pipe = dp->fpipe[part] != 0;
-  switch (d.w) {
-    case 4:
-      if (pipe) hipLaunchKernelGGL((fused_pass_kernel<T, 4, true>), grid, dim3(256), 0, str, st, fd, um, xcd);
-      else hipLaunchKernelGGL((fused_pass_kernel<T, 4, false>), grid, dim3(256), 0, str, st, fd, um, xcd);
-      break;
-    case 5:
-      if (pipe) hipLaunchKernelGGL((fused_pass_kernel<T, 5, true>), grid, dim3(256), 0, str, st, fd, um, xcd);
-      else hipLaunchKernelGGL((fused_pass_kernel<T, 5, false>), grid, dim3(256), 0, str, st, fd, um, xcd);
-      break;
-    case 6: hipLaunchKernelGGL((fused_pass_kernel<T, 6, false>), grid, dim3(256), 0, str, st, fd, um, xcd); break;
-    case 7: hipLaunchKernelGGL((fused_pass_kernel<T, 7, false>), grid, dim3(256), 0, str, st, fd, um, xcd); break;
-    default: return fail(HS_E_UNSUPPORTED, "part %d has no fused form", part);
-  }
-  HIP_TRY(hipGetLastError());
-  return HS_OK;
-}
-
-hs_status dev_run_fused(State* s, Plan* p, int part) {
+hs_status dev_run_fused(State* s, Plan* p, int part, bool of_set) {
   HIP_TRY(hipSetDevice(s->device));
-  DevicePlan* dp = nullptr;
+  const int dt = (int)s->dtype;
+  DeviceFused* dp = nullptr;
   {
     std::lock_guard<std::mutex> lk(p->mu);
-    if (hs_status rc = device_plan(s, p, false, &dp)) return rc;
-    if (!dp->fused_ready) {
-      hs_status rc = s->dtype == HS_C64 ? upload_fused<float>(p, dp) : upload_fused<double>(p, dp);
+    auto it = p->fdev[of_set][dt].find(s->device);
+    if (it != p->fdev[of_set][dt].end()) {
+      dp = it->second;
+    } else {
+      const std::vector<FusedPart>& parts = of_set ? p->fused_set[dt].parts : p->fused;
+      hs_status rc = s->dtype == HS_C64 ? upload_fused<float>(parts, s->device, &dp)
+                                        : upload_fused<double>(parts, s->device, &dp);
       if (rc) return rc;
+      p->fdev[of_set][dt][s->device] = dp;
     }
   }
-  return s->dtype == HS_C64 ? launch_fused<float>(s, dp, part) : launch_fused<double>(s, dp, part);
+  FusedLaunch& l = dp->launch[part];
+  if (!l.w) return fail(HS_E_UNSUPPORTED, "part %d has no fused form", part);
+  void* st = s->ptr;
+  const FusedDesc* fd = dp->parts + part;
+  void* args[] = {&st, &fd, &dp->mat, &l.xcd, &l.chunk};  // the plain kernels have no fifth argument
+  HIP_TRY(hipLaunchKernel(l.fn, dim3(l.grid), dim3(l.block), args, 0, stream_of(s)));
+  return HS_OK;
 }
 
 // ---- readout ----------------------------------------------------------------

@@ -26,7 +26,7 @@ def test_sweeps_are_counted():
         assert plan.sweep_source(plan.num_sweeps(dtype) - 1, dtype).startswith("#ifndef")
         with pytest.raises(hisv.HisvError):
             plan.sweep_source(plan.num_sweeps(dtype), dtype)
-    assert plan.num_sweeps("c64", "part_fused") == plan.num_parts
+    assert plan.num_sweeps("c64", "part_fused") <= plan.num_parts
     assert plan.num_sweeps("c64", "gate_per_pass") == len(gates)
 
 
@@ -70,6 +70,43 @@ def test_sweeps_gpu(n, dtype):
         for i in range(plan.num_parts):
             st.simulate_part(plan, i, mode)
         np.testing.assert_allclose(st.amplitudes(), want, atol=TOL[dtype], rtol=0, err_msg=f"parts {mode}")
+    st.close()
+
+
+def test_dense_pieces_are_counted():
+    n, gates = 16, wl.dressed_pairs_circuit(16, 200, 1, span=5, dwell=16)
+    plan = make(n, gates, 5)
+    for dtype in ("c64", "c128"):
+        assert plan.num_sweeps(dtype, "part_fused") <= 0.9 * plan.num_parts
+    # a part without a fused form: nothing is cut anew, hs_simulate reports it
+    wide = make(n, wl.layered_circuit(n, 3, 1), 8)
+    assert wide.num_sweeps("c64", "part_fused") == wide.num_parts
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [8, 9, 10, 11, 12, 15])
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+def test_dense_pieces_gpu(n, dtype):
+    """Every width of the fused kernels from the smallest state they take
+    (fewer tiles than the waves of one workgroup, one chunk, several chunks),
+    part by part and cut anew."""
+    torch = pytest.importorskip("torch")
+    buf = torch.empty(1 << n, dtype={"c64": torch.complex64, "c128": torch.complex128}[dtype], device="cuda")
+    st = hisv.State.wrap_tensor(buf, torch.cuda.current_stream())
+    for w in range(4, min(7, n - 4) + 1):
+        for seed, gates in ((1, wl.dressed_pairs_circuit(n, 60, w, span=4, dwell=9)),
+                            (2, wl.random_circuit(n, 80, ("h", "u3", "rz", "cx", "cp", "swap"), w))):
+            x = wl.random_basis_index(n, seed)
+            want = sv.simulate(n, gates, sv.basis_state(n, x))
+            plan = make(n, gates, w)
+            print(f"[case] n={n} {dtype} w={w} seed={seed} {plan.num_parts} parts", flush=True)
+            st.set_basis(x)
+            st.simulate(plan, "part_fused")
+            np.testing.assert_allclose(st.amplitudes(), want, atol=TOL[dtype], rtol=0, err_msg=f"pieces w={w}")
+            st.set_basis(x)
+            for i in range(plan.num_parts):
+                st.simulate_part(plan, i, "part_fused")
+            np.testing.assert_allclose(st.amplitudes(), want, atol=TOL[dtype], rtol=0, err_msg=f"parts w={w}")
     st.close()
 
 
