@@ -343,6 +343,7 @@ hs_status hs_state_destroy(hs_state s) {
       const hipError_t f = hipFree(s->scratch);
       if (e == hipSuccess) e = f;
     }
+    dev_read_stage_free(&s->stage);
     delete s;
     if (e != hipSuccess) return fail(HS_E_HIP, "state teardown: %s", hipGetErrorString(e));
     return HS_OK;

@@ -240,6 +240,14 @@ hs_status plan_sweeps(Plan* p, hs_dtype dtype, bool spec, const SweepSet** out);
 const std::vector<CompiledPart>& compiled_parts(const Plan* p, hs_dtype dtype, hs_exec exec);
 
 // ---- state --------------------------------------------------------------------
+// Pinned host buffers and events of readouts (kernels.hip).
+struct ReadStage {
+  void* buf = nullptr;
+  void* done[2] = {nullptr, nullptr};  // hipEvent_t, after the kernel that filled a buffer
+};
+hs_status dev_read_stage_create(ReadStage* r);
+void dev_read_stage_free(ReadStage* r);
+
 struct State {
   int n = 0;
   hs_dtype dtype = HS_C64;
@@ -248,8 +256,9 @@ struct State {
   bool owned = false;
   int device = 0;
   void* stream = nullptr;   // hipStream_t
-  void* scratch = nullptr;  // device scratch for readout (lazily allocated)
+  void* scratch = nullptr;  // device scratch of the norm (lazily allocated)
   size_t scratch_bytes = 0;
+  ReadStage stage;          // made on the first readout
 };
 
 inline size_t amp_bytes(hs_dtype d) { return d == HS_C64 ? 8 : 16; }

@@ -860,48 +860,99 @@ __device__ __forceinline__ Walk stream_walk(uint64_t count, uint32_t xcd) {
           (uint64_t)(gridDim.x >> 3) * blockDim.x, (x + 1) * per};
 }
 
+// VEC consecutive amplitudes, moved as one 16 B access: two of a complex64
+// state (where its address allows it), one of a complex128 state.
+template <typename T, int VEC>
+struct alignas(VEC * 2 * sizeof(T)) Amps {
+  cplx<T> a[VEC];
+};
+
 template <typename T>
+__device__ __forceinline__ void pair_1q(const M2<T>& u, cplx<T>& x, cplx<T>& y) {
+  cplx<T> r0, r1;
+  r0.x = u.c[0] * x.x - u.c[1] * x.y + u.c[2] * y.x - u.c[3] * y.y;
+  r0.y = u.c[0] * x.y + u.c[1] * x.x + u.c[2] * y.y + u.c[3] * y.x;
+  r1.x = u.c[4] * x.x - u.c[5] * x.y + u.c[6] * y.x - u.c[7] * y.y;
+  r1.y = u.c[4] * x.y + u.c[5] * x.x + u.c[6] * y.y + u.c[7] * y.x;
+  x = r0;
+  y = r1;
+}
+
+// index with a zero bit inserted at position q
+__device__ __forceinline__ uint64_t insert_zero(uint64_t p, int q) {
+  return ((p >> q) << (q + 1)) | (p & ((uint64_t(1) << q) - 1));
+}
+
+// One-qubit sweep over pairs of vectors; q counts vectors (the qubit less
+// log2(VEC)).  q = -1: the pair is inside the vector (qubit 0, VEC = 2).
+template <typename T, int VEC>
 __global__ void __launch_bounds__(256)
-gate_pass_1q(cplx<T>* __restrict__ st, int q, uint64_t npairs, M2<T> u, uint32_t xcd) {
-  const Walk w = stream_walk(npairs, xcd);
-  const uint64_t lowmask = (uint64_t(1) << q) - 1;
+gate_pass_1q(Amps<T, VEC>* __restrict__ st, int q, uint64_t count, M2<T> u, uint32_t xcd) {
+  const Walk w = stream_walk(count, xcd);
   for (uint64_t p = w.first; p < w.end; p += w.step) {
-    const uint64_t i0 = ((p >> q) << (q + 1)) | (p & lowmask);
-    const uint64_t i1 = i0 | (uint64_t(1) << q);
-    const cplx<T> x = st[i0], y = st[i1];
-    cplx<T> r0, r1;
-    r0.x = u.c[0] * x.x - u.c[1] * x.y + u.c[2] * y.x - u.c[3] * y.y;
-    r0.y = u.c[0] * x.y + u.c[1] * x.x + u.c[2] * y.y + u.c[3] * y.x;
-    r1.x = u.c[4] * x.x - u.c[5] * x.y + u.c[6] * y.x - u.c[7] * y.y;
-    r1.y = u.c[4] * x.y + u.c[5] * x.x + u.c[6] * y.y + u.c[7] * y.x;
-    st[i0] = r0;
-    st[i1] = r1;
+    if (VEC == 2 && q < 0) {
+      Amps<T, VEC> s = st[p];
+      pair_1q(u, s.a[0], s.a[VEC - 1]);
+      st[p] = s;
+      continue;
+    }
+    const uint64_t i0 = insert_zero(p, q), i1 = i0 | (uint64_t(1) << q);
+    Amps<T, VEC> x = st[i0], y = st[i1];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) pair_1q(u, x.a[v], y.a[v]);
+    st[i0] = x;
+    st[i1] = y;
   }
 }
 
-// kind: 0 CX(q0 control, q1 target), 1 CZ, 2 CP(c0, c1), 3 SWAP
-template <typename T>
+// Diagonal one-qubit sweep: amplitudes times d0 or d1 by their bit.  HALF
+// (d0 = 1): only the vectors with the bit set are touched.
+template <typename T, int VEC, bool HALF>
 __global__ void __launch_bounds__(256)
-gate_pass_2q(cplx<T>* __restrict__ st, int q0, int q1, int kind, uint64_t nquads, T cr, T ci,
-             uint32_t xcd) {
+gate_pass_diag(Amps<T, VEC>* __restrict__ st, int q, uint64_t count, cplx<T> d0, cplx<T> d1, uint32_t xcd) {
+  const Walk w = stream_walk(count, xcd);
+  for (uint64_t p = w.first; p < w.end; p += w.step) {
+    const uint64_t i = HALF ? insert_zero(p, q) | (uint64_t(1) << q) : p;
+    Amps<T, VEC> s = st[i];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+      const bool one = HALF || (q < 0 ? v != 0 : (i >> q & 1) != 0);
+      cmul(s.a[v], one ? d1.x : d0.x, one ? d1.y : d0.y);
+    }
+    st[i] = s;
+  }
+}
+
+// Two-qubit sweep: only the amplitudes the gate changes are read and written --
+// half of the state for CX (control set) and SWAP (bits different), a quarter
+// for CZ and CP (both set), where reading the whole quad moved three quarters.
+// Bits count vectors.  KIND: 0 CX(q0 control, q1 target), 1 CZ, 2 CP(c), 3 SWAP
+template <typename T, int VEC, int KIND>
+__global__ void __launch_bounds__(256)
+gate_pass_2q(Amps<T, VEC>* __restrict__ st, int q0, int q1, uint64_t count, cplx<T> c, uint32_t xcd) {
   const int lo = min(q0, q1), hi = max(q0, q1);
-  const Walk w = stream_walk(nquads, xcd);
+  const Walk w = stream_walk(count, xcd);
   const uint64_t m0 = uint64_t(1) << q0, m1 = uint64_t(1) << q1;
   for (uint64_t p = w.first; p < w.end; p += w.step) {
-    uint64_t i = ((p >> lo) << (lo + 1)) | (p & ((uint64_t(1) << lo) - 1));
-    i = ((i >> hi) << (hi + 1)) | (i & ((uint64_t(1) << hi) - 1));
-    // a[b] with bit 0 of b = qubit q0, bit 1 = qubit q1
-    cplx<T> a0 = st[i], a1 = st[i | m0], a2 = st[i | m1], a3 = st[i | m0 | m1];
-    if (kind == 0) {
-      const cplx<T> t = a1; a1 = a3; a3 = t;
-    } else if (kind == 1) {
-      a3.x = -a3.x; a3.y = -a3.y;
-    } else if (kind == 2) {
-      cmul(a3, cr, ci);
+    const uint64_t i = insert_zero(insert_zero(p, lo), hi);
+    if constexpr (KIND == 0 || KIND == 3) {
+      const uint64_t j = i | m0, k = KIND == 0 ? i | m0 | m1 : i | m1;
+      const Amps<T, VEC> x = st[j], y = st[k];
+      st[j] = y;
+      st[k] = x;
     } else {
-      const cplx<T> t = a1; a1 = a2; a2 = t;
+      Amps<T, VEC> s = st[i | m0 | m1];
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) {
+        if constexpr (KIND == 1) {
+          s.a[v].x = -s.a[v].x;
+          s.a[v].y = -s.a[v].y;
+        } else {
+          cmul(s.a[v], c.x, c.y);
+        }
+      }
+      st[i | m0 | m1] = s;
     }
-    st[i] = a0; st[i | m0] = a1; st[i | m1] = a2; st[i | m0 | m1] = a3;
   }
 }
 
@@ -932,7 +983,17 @@ norm_partial(const cplx<T>* __restrict__ st, uint64_t N, double* __restrict__ pa
   __shared__ double sh[kNormThreads];
   double acc = 0.0;
   const uint64_t stride = (uint64_t)kNormBlocks * kNormThreads;
-  for (uint64_t i = (uint64_t)blockIdx.x * kNormThreads + threadIdx.x; i < N; i += stride) {
+  uint64_t i = (uint64_t)blockIdx.x * kNormThreads + threadIdx.x;
+  // eight loads in flight a thread, added up in the same order (one at a time
+  // leaves HBM waiting: 27 qubits complex64 3.6 TB/s)
+  for (; i + 7 * stride < N; i += 8 * stride) {
+    cplx<T> v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = st[i + k * stride];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc += (double)v[k].x * (double)v[k].x + (double)v[k].y * (double)v[k].y;
+  }
+  for (; i < N; i += stride) {
     const cplx<T> v = st[i];
     acc += (double)v.x * (double)v.x + (double)v.y * (double)v.y;
   }
@@ -1064,36 +1125,55 @@ static void sweep_grid(uint64_t work, unsigned* grid, uint32_t* xcd) {
   *grid = (unsigned)g;
 }
 
-template <typename T>
-static hs_status gate_pass_t(State* s, const Gate& g) {
-  const uint64_t N = uint64_t(1) << s->n;
+// One gate as a sweep, on vectors of VEC amplitudes where its qubits allow it.
+template <typename T, int VEC>
+static hs_status gate_pass_v(State* s, const Gate& g) {
+  constexpr int L = VEC == 2 ? 1 : 0;
+  const uint64_t N = uint64_t(1) << (s->n - L);  // vectors
+  auto* st = (Amps<T, VEC>*)s->ptr;
+  const int q = g.q0 - L;
   unsigned grid;
   uint32_t xcd;
   if (g.arity() == 1) {
-    sweep_grid(N / 2, &grid, &xcd);
     cd u[4];
     gate_matrix(g, u);
-    M2<T> m;
-    for (int i = 0; i < 4; ++i) {
-      m.c[2 * i] = (T)u[i].real();
-      m.c[2 * i + 1] = (T)u[i].imag();
+    if (u[1] == cd(0, 0) && u[2] == cd(0, 0)) {
+      const cplx<T> d0{(T)u[0].real(), (T)u[0].imag()}, d1{(T)u[3].real(), (T)u[3].imag()};
+      const bool half = u[0] == cd(1, 0) && q >= 0;
+      sweep_grid(half ? N / 2 : N, &grid, &xcd);
+      if (half)
+        hipLaunchKernelGGL((gate_pass_diag<T, VEC, true>), dim3(grid), dim3(256), 0, stream_of(s), st, q, N / 2, d0,
+                           d1, xcd);
+      else
+        hipLaunchKernelGGL((gate_pass_diag<T, VEC, false>), dim3(grid), dim3(256), 0, stream_of(s), st, q, N, d0, d1,
+                           xcd);
+    } else {
+      M2<T> m;
+      for (int i = 0; i < 4; ++i) {
+        m.c[2 * i] = (T)u[i].real();
+        m.c[2 * i + 1] = (T)u[i].imag();
+      }
+      const uint64_t items = q < 0 ? N : N / 2;
+      sweep_grid(items, &grid, &xcd);
+      hipLaunchKernelGGL((gate_pass_1q<T, VEC>), dim3(grid), dim3(256), 0, stream_of(s), st, q, items, m, xcd);
     }
-    hipLaunchKernelGGL(gate_pass_1q<T>, dim3(grid), dim3(256), 0, stream_of(s),
-                       (cplx<T>*)s->ptr, g.q0, N / 2, m, xcd);
   } else {
-    if (s->n < 2) return fail(HS_E_ARG, "two-qubit gate on a 1-qubit state");
+    const int p = g.q1 - L;
+    cplx<T> c{0, 0};
     sweep_grid(N / 4, &grid, &xcd);
-    int kind = 0;
-    T cr = 0, ci = 0;
+#define HS_GATE_2Q(KIND_)                                                                                         \
+  hipLaunchKernelGGL((gate_pass_2q<T, VEC, KIND_>), dim3(grid), dim3(256), 0, stream_of(s), st, q, p, N / 4, c, xcd)
     switch (g.kind) {
-      case HS_CX: kind = 0; break;
-      case HS_CZ: kind = 1; break;
-      case HS_CP: kind = 2; cr = (T)cos(g.p[0]); ci = (T)sin(g.p[0]); break;
-      case HS_SWAP: kind = 3; break;
+      case HS_CX: HS_GATE_2Q(0); break;
+      case HS_CZ: HS_GATE_2Q(1); break;
+      case HS_CP:
+        c = {(T)cos(g.p[0]), (T)sin(g.p[0])};
+        HS_GATE_2Q(2);
+        break;
+      case HS_SWAP: HS_GATE_2Q(3); break;
       default: return fail(HS_E_ARG, "unknown two-qubit kind %d", g.kind);
     }
-    hipLaunchKernelGGL(gate_pass_2q<T>, dim3(grid), dim3(256), 0, stream_of(s),
-                       (cplx<T>*)s->ptr, g.q0, g.q1, kind, N / 4, cr, ci, xcd);
+#undef HS_GATE_2Q
   }
   HIP_TRY(hipGetLastError());
   return HS_OK;
@@ -1101,7 +1181,13 @@ static hs_status gate_pass_t(State* s, const Gate& g) {
 
 hs_status dev_gate_pass(State* s, const Gate& g) {
   HIP_TRY(hipSetDevice(s->device));
-  return s->dtype == HS_C64 ? gate_pass_t<float>(s, g) : gate_pass_t<double>(s, g);
+  if (g.arity() == 2 && s->n < 2) return fail(HS_E_ARG, "two-qubit gate on a 1-qubit state");
+  if (s->dtype == HS_C128) return gate_pass_v<double, 1>(s, g);
+  // pairs of complex64 amplitudes as 16 B accesses, unless the state starts
+  // inside one (hs_state_wrap asks for the alignment of an amplitude) or a
+  // two-qubit gate acts on qubit 0
+  const bool pairs = (uintptr_t)s->ptr % 16 == 0 && (g.arity() == 1 || (g.q0 > 0 && g.q1 > 0));
+  return pairs ? gate_pass_v<float, 2>(s, g) : gate_pass_v<float, 1>(s, g);
 }
 
 // ---- uploaded plan ----------------------------------------------------------
@@ -1620,11 +1706,69 @@ static hs_status ensure_scratch(State* s, size_t bytes) {
   return HS_OK;
 }
 
+// Pinned staging of readouts, made on a state's first one: two buffers that
+// the readout kernels write over PCIe, one being copied out by the host while
+// the kernel of the next chunk fills the other.  (Device scratch, a copy into
+// the caller's pageable memory and a wait for every chunk took 615 us for 2^20
+// probabilities of a 27-qubit state and 28 us for 4,096 amplitudes.)
+constexpr size_t kStageBytes = size_t(1) << 20;
+
+hs_status dev_read_stage_create(ReadStage* r) {
+  if (r->buf) return HS_OK;
+  void* buf = nullptr;
+  if (hipHostMalloc(&buf, 2 * kStageBytes, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(HS_E_NOMEM, "pinned readout staging of %zu bytes", 2 * kStageBytes);
+  }
+  r->buf = buf;
+  for (void*& ev : r->done) {
+    hipEvent_t e = nullptr;
+    HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+    ev = e;
+  }
+  return HS_OK;
+}
+
+void dev_read_stage_free(ReadStage* r) {
+  for (void*& ev : r->done) {
+    if (ev) (void)hipEventDestroy((hipEvent_t)ev);
+    ev = nullptr;
+  }
+  if (r->buf) (void)hipHostFree(r->buf);
+  r->buf = nullptr;
+}
+
+// `count` items in chunks of `chunk` through the two buffers: launch(b, done, c)
+// queues the kernel of items [done, done + c) on buffer b, take(b, done, c)
+// copies them out.
+template <typename Launch, typename Take>
+static hs_status staged(State* s, uint64_t count, uint64_t chunk, Launch&& launch, Take&& take) {
+  uint64_t queued = 0;
+  for (uint64_t done = 0, i = 0; done < count; ++i) {
+    while (queued < count && queued < (i + 2) * chunk) {
+      const uint64_t c = std::min(chunk, count - queued);
+      const int b = (int)(queued / chunk & 1);
+      if (hs_status rc = launch(b, queued, c)) {
+        (void)hipStreamSynchronize(stream_of(s));  // the other buffer's kernel may be running
+        return rc;
+      }
+      HIP_TRY(hipEventRecord((hipEvent_t)s->stage.done[b], stream_of(s)));
+      queued += c;
+    }
+    const uint64_t c = std::min(chunk, count - done);
+    HIP_TRY(hipEventSynchronize((hipEvent_t)s->stage.done[i & 1]));
+    take((int)(i & 1), done, c);
+    done += c;
+  }
+  return HS_OK;
+}
+
 hs_status dev_norm(State* s, double* out) {
   HIP_TRY(hipSetDevice(s->device));
-  if (hs_status rc = ensure_scratch(s, (kNormBlocks + 8) * sizeof(double))) return rc;
+  if (hs_status rc = ensure_scratch(s, kNormBlocks * sizeof(double))) return rc;
+  if (hs_status rc = dev_read_stage_create(&s->stage)) return rc;
   double* part = (double*)s->scratch;
-  double* res = part + kNormBlocks;
+  double* res = (double*)s->stage.buf;
   const uint64_t N = uint64_t(1) << s->n;
   if (s->dtype == HS_C64)
     hipLaunchKernelGGL(norm_partial<float>, dim3(kNormBlocks), dim3(kNormThreads), 0, stream_of(s),
@@ -1634,8 +1778,8 @@ hs_status dev_norm(State* s, double* out) {
                        (const cplx<double>*)s->ptr, N, part);
   hipLaunchKernelGGL(norm_final, dim3(1), dim3(kNormThreads), 0, stream_of(s), part, res);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipMemcpyAsync(out, res, sizeof(double), hipMemcpyDeviceToHost, stream_of(s)));
   HIP_TRY(hipStreamSynchronize(stream_of(s)));
+  *out = *res;
   return HS_OK;
 }
 
@@ -1693,54 +1837,50 @@ hs_status dev_norm_noalloc(State* s, double* out) {
 
 hs_status dev_read(State* s, uint64_t first, uint64_t count, double* out, bool probs) {
   HIP_TRY(hipSetDevice(s->device));
-  const uint64_t chunk = uint64_t(1) << 22;
-  if (hs_status rc = ensure_scratch(s, std::max<size_t>(chunk * 16, (kNormBlocks + 8) * 8))) return rc;
-  const int per = probs ? 1 : 2;
-  for (uint64_t done = 0; done < count;) {
-    const uint64_t c = std::min(chunk, count - done);
-    unsigned grid;
-    if (hs_status rc = stream_grid(s->device, c, &grid)) return rc;
-    if (s->dtype == HS_C64)
-      hipLaunchKernelGGL(readout_kernel<float>, dim3(grid), dim3(256), 0, stream_of(s),
-                         (const cplx<float>*)s->ptr, first + done, c, probs ? 1 : 0, (double*)s->scratch);
-    else
-      hipLaunchKernelGGL(readout_kernel<double>, dim3(grid), dim3(256), 0, stream_of(s),
-                         (const cplx<double>*)s->ptr, first + done, c, probs ? 1 : 0, (double*)s->scratch);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(out + done * per, s->scratch, c * per * sizeof(double),
-                           hipMemcpyDeviceToHost, stream_of(s)));
-    HIP_TRY(hipStreamSynchronize(stream_of(s)));
-    done += c;
-  }
-  return HS_OK;
+  if (hs_status rc = dev_read_stage_create(&s->stage)) return rc;
+  const uint64_t per = probs ? 1 : 2, chunk = kStageBytes / (per * sizeof(double));
+  auto buffer = [&](int b) { return (double*)((char*)s->stage.buf + b * kStageBytes); };
+  return staged(
+      s, count, chunk,
+      [&](int b, uint64_t at, uint64_t c) -> hs_status {
+        unsigned grid;
+        if (hs_status rc = stream_grid(s->device, c, &grid)) return rc;
+        if (s->dtype == HS_C64)
+          hipLaunchKernelGGL(readout_kernel<float>, dim3(grid), dim3(256), 0, stream_of(s),
+                             (const cplx<float>*)s->ptr, first + at, c, probs ? 1 : 0, buffer(b));
+        else
+          hipLaunchKernelGGL(readout_kernel<double>, dim3(grid), dim3(256), 0, stream_of(s),
+                             (const cplx<double>*)s->ptr, first + at, c, probs ? 1 : 0, buffer(b));
+        HIP_TRY(hipGetLastError());
+        return HS_OK;
+      },
+      [&](int b, uint64_t at, uint64_t c) { std::memcpy(out + at * per, buffer(b), c * per * sizeof(double)); });
 }
 
 // Amplitudes at host-given indices (validated < 2^n by the caller), widened
-// to complex128, in chunks through the state's scratch buffer.
+// to complex128; the kernel reads the indices from the staging buffer too.
 hs_status dev_read_at(State* s, const uint64_t* idx, uint64_t count, double* out) {
   HIP_TRY(hipSetDevice(s->device));
-  const uint64_t chunk = uint64_t(1) << 21;  // 16 MiB of indices + 32 MiB of output
-  if (hs_status rc = ensure_scratch(s, chunk * 24)) return rc;
-  uint64_t* didx = (uint64_t*)s->scratch;
-  double* dout = (double*)((char*)s->scratch + chunk * 8);
-  for (uint64_t done = 0; done < count;) {
-    const uint64_t c = std::min(chunk, count - done);
-    unsigned grid;
-    if (hs_status rc = stream_grid(s->device, c, &grid)) return rc;
-    HIP_TRY(hipMemcpyAsync(didx, idx + done, c * sizeof(uint64_t), hipMemcpyHostToDevice, stream_of(s)));
-    if (s->dtype == HS_C64)
-      hipLaunchKernelGGL(gather_kernel<float>, dim3(grid), dim3(256), 0, stream_of(s),
-                         (const cplx<float>*)s->ptr, didx, c, dout);
-    else
-      hipLaunchKernelGGL(gather_kernel<double>, dim3(grid), dim3(256), 0, stream_of(s),
-                         (const cplx<double>*)s->ptr, didx, c, dout);
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(hipMemcpyAsync(out + 2 * done, dout, c * 2 * sizeof(double), hipMemcpyDeviceToHost,
-                           stream_of(s)));
-    HIP_TRY(hipStreamSynchronize(stream_of(s)));
-    done += c;
-  }
-  return HS_OK;
+  if (hs_status rc = dev_read_stage_create(&s->stage)) return rc;
+  const uint64_t chunk = kStageBytes / 32;  // 256 KiB of indices, 512 KiB of output
+  auto indices = [&](int b) { return (uint64_t*)((char*)s->stage.buf + b * kStageBytes); };
+  auto values = [&](int b) { return (double*)(indices(b) + chunk); };
+  return staged(
+      s, count, chunk,
+      [&](int b, uint64_t at, uint64_t c) -> hs_status {
+        unsigned grid;
+        if (hs_status rc = stream_grid(s->device, c, &grid)) return rc;
+        std::memcpy(indices(b), idx + at, c * sizeof(uint64_t));
+        if (s->dtype == HS_C64)
+          hipLaunchKernelGGL(gather_kernel<float>, dim3(grid), dim3(256), 0, stream_of(s),
+                             (const cplx<float>*)s->ptr, indices(b), c, values(b));
+        else
+          hipLaunchKernelGGL(gather_kernel<double>, dim3(grid), dim3(256), 0, stream_of(s),
+                             (const cplx<double>*)s->ptr, indices(b), c, values(b));
+        HIP_TRY(hipGetLastError());
+        return HS_OK;
+      },
+      [&](int b, uint64_t at, uint64_t c) { std::memcpy(out + 2 * at, values(b), c * 2 * sizeof(double)); });
 }
 
 hs_status dev_copy_probe(const void* src, void* dst, size_t bytes, void* stream) {

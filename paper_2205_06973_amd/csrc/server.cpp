@@ -85,7 +85,6 @@ struct Request {
 };
 
 constexpr int kPrepThreads = 4;
-constexpr size_t kReadScratch = size_t(64) << 20;  // covers dev_read's largest chunk
 constexpr size_t kPinnedStaging = size_t(8) << 20;  // descriptor staging per preparing thread
 // Parts a request enqueues at a time (hs_tune "serve_chunk", default 8,
 // read at launch).  A hardware queue runs its commands in order, so a
@@ -107,7 +106,7 @@ struct hs_server_ {
   std::vector<hipStream_t> prep_streams;
   std::vector<PinnedStaging> pins;  // one per preparing thread
   hipStream_t read_stream = nullptr;
-  void* read_scratch = nullptr;  // persistent staging of hs_server_read
+  ReadStage read_stage;  // persistent staging of hs_server_read
   std::mutex read_mu;
   std::mutex mu;
   std::condition_variable cv;
@@ -418,7 +417,7 @@ hs_status hs_server_create(size_t budget_bytes, int num_streams, hs_server* out)
         if (p.busy) (void)hipEventDestroy((hipEvent_t)p.busy);
       }
       if (sv->read_stream) (void)hipStreamDestroy(sv->read_stream);
-      if (sv->read_scratch) (void)hipFree(sv->read_scratch);
+      dev_read_stage_free(&sv->read_stage);
     };
     for (int i = 0; i < num_streams; ++i) {
       hipStream_t s;
@@ -455,11 +454,9 @@ hs_status hs_server_create(size_t budget_bytes, int num_streams, hs_server* out)
       cleanup();
       return fail(HS_E_HIP, "hipStreamCreate failed");
     }
-    if (hipMalloc(&sv->read_scratch, kReadScratch) != hipSuccess) {
-      (void)hipGetLastError();
-      sv->read_scratch = nullptr;
+    if (hs_status rc = dev_read_stage_create(&sv->read_stage)) {
       cleanup();
-      return fail(HS_E_NOMEM, "read staging buffer of %zu bytes", kReadScratch);
+      return rc;
     }
     hs_server_* raw = sv.get();
     try {
@@ -584,8 +581,7 @@ hs_status hs_server_read(hs_server sv, uint64_t ticket, uint64_t first, uint64_t
       std::lock_guard<std::mutex> rl(sv->read_mu);
       view.stream = sv->read_stream;
       view.owned = false;
-      view.scratch = sv->read_scratch;
-      view.scratch_bytes = kReadScratch;
+      view.stage = sv->read_stage;
       rc = dev_read(&view, first, count, out, false);
     }
     std::lock_guard<std::mutex> lk(sv->mu);
@@ -703,7 +699,7 @@ hs_status hs_server_destroy(hs_server sv) {
     }
     (void)hipStreamSynchronize(sv->read_stream);
     (void)hipStreamDestroy(sv->read_stream);
-    if (sv->read_scratch) (void)hipFree(sv->read_scratch);
+    dev_read_stage_free(&sv->read_stage);
     for (PinnedStaging& p : sv->pins) {  // every copy from them has run
       if (p.ptr) (void)hipHostFree(p.ptr);
       if (p.busy) (void)hipEventDestroy((hipEvent_t)p.busy);
