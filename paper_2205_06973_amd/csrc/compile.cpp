@@ -209,7 +209,15 @@ struct Split {
 
 // M = S L K with L allowed by `role`; the cheapest of a few candidates.
 Split split_gate(const cd M[4], Role role) {
-  const cd a = M[0], b = M[1], c = M[2], d = M[3], zero(0, 0);
+  // scale: M may be a unitary times a number
+  const double unit = std::max(std::abs(M[0]), std::abs(M[1]));
+  if (!(unit > 0)) {
+    Split whole;
+    std::copy(M, M + 4, whole.K);
+    whole.cost = pair_cost(M);
+    return whole;
+  }
+  const cd a = M[0] / unit, b = M[1] / unit, c = M[2] / unit, d = M[3] / unit, zero(0, 0);
   Split best;
   auto offer = [&](cd S, cd l0, cd l1, cd l2, cd l3, cd k0, cd k1, cd k2, cd k3) {
     Split s;
@@ -253,12 +261,75 @@ Split split_gate(const cd M[4], Role role) {
         offer(ph * w1, cd(ct, 0), cd(0, -sn), cd(0, -sn), cd(ct, 0), 1, cd(-y1, -x1) / w1, cd(y1, -x1) / w1, 1);
     }
   }
-  if (best.rank >= 1e30) {  // not a unitary: keep it as it is
-    for (int i = 0; i < 4; ++i) best.K[i] = M[i];
-    best.cost = pair_cost(best.K);
-  }
+  best.S *= unit;
   return best;
 }
+
+}  // namespace
+
+// What hs_simulate's sweeps are cut from: the circuit with every run of
+// one-qubit gates split as above, L carried on to the qubit's next gate --
+// also where that lies in another sweep -- and K (scaled to a unitary) left as
+// one matrix gate.  A part on its own has to finish every run it holds; over
+// the circuit only the last run of each qubit is left (instructions an
+// amplitude of the specialized kernels, 28-qubit layered circuit of 40 layers:
+// 5,650 with every sweep finishing its runs, 4,900 this way).
+std::vector<Gate> reduce_gates(int n, const std::vector<Gate>& gates) {
+  std::vector<Gate> out;
+  out.reserve(gates.size());
+  std::vector<std::array<cd, 4>> pend(n);
+  std::vector<char> has(n, 0);
+  cd phase = 1;
+  int last = -1;  // a matrix gate to carry the phase
+  auto put = [&](int q, const cd u[4]) {
+    Gate g{};
+    g.kind = kMatrixGate;
+    g.q0 = q;
+    g.q1 = -1;
+    std::copy(u, u + 4, g.u);
+    last = (int)out.size();
+    out.push_back(g);
+  };
+  auto flush = [&](int q, Role role) {
+    if (!has[q]) return;
+    Split f = split_gate(pend[q].data(), role);
+    const double mag = std::abs(f.S);
+    phase *= f.S / mag;
+    std::copy(f.L, f.L + 4, pend[q].begin());
+    has[q] = !is_identity(f.L);
+    if (is_identity(f.K)) return;
+    for (cd& z : f.K) z *= mag;
+    put(q, f.K);
+  };
+  for (const Gate& g : gates) {
+    if (g.arity() == 1) {
+      cd u[4];
+      gate_matrix(g, u);
+      if (has[g.q0]) matmul2(u, pend[g.q0].data(), pend[g.q0].data());
+      else std::copy(u, u + 4, pend[g.q0].begin());
+      has[g.q0] = 1;
+      continue;
+    }
+    if (g.kind == HS_SWAP) {
+      std::swap(pend[g.q0], pend[g.q1]);
+      std::swap(has[g.q0], has[g.q1]);
+    } else {
+      flush(g.q0, kRoleZ);
+      flush(g.q1, g.kind == HS_CX ? kRoleX : kRoleZ);
+    }
+    out.push_back(g);
+  }
+  for (int q = 0; q < n; ++q) flush(q, kRoleLast);
+  if (clean(phase) != cd(1, 0)) {
+    const cd d[4] = {phase, 0, 0, phase};
+    if (last < 0) put(0, d);
+    else
+      for (cd& z : out[last].u) z *= phase;
+  }
+  return out;
+}
+
+namespace {
 
 // Vector instructions an amplitude for one op on the kernels.
 double op_work(const HostOp& op) {

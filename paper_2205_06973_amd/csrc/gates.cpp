@@ -115,6 +115,9 @@ void gate_matrix(const Gate& g, cd u[4]) {
   const cd I(0.0, 1.0);
   const double th = g.p[0];
   switch (g.kind) {
+    case kMatrixGate:
+      for (int i = 0; i < 4; ++i) u[i] = g.u[i];
+      return;
     case HS_H: {
       const double r = 1.0 / sqrt(2.0);
       u[0] = r; u[1] = r; u[2] = r; u[3] = -r;

@@ -42,9 +42,11 @@ hs_status guarded(F&& body) noexcept {
 }
 
 // ---- gates (Sec. II.A) ----------------------------------------------------
+constexpr int kMatrixGate = 100;  // internal kind: the one-qubit matrix in Gate::u
 struct Gate {
   int kind, q0, q1;
   double p[3];
+  cd u[4];  // kMatrixGate only
   int arity() const { return q1 < 0 ? 1 : 2; }
   uint64_t mask() const {
     return (uint64_t(1) << q0) | (q1 >= 0 ? (uint64_t(1) << q1) : 0);
@@ -156,6 +158,9 @@ struct CompileOptions {
   LaunchShape launch;
 };
 
+// The same circuit with its one-qubit gates as few matrices (compile.cpp).
+std::vector<Gate> reduce_gates(int n, const std::vector<Gate>& gates);
+
 // Compile one part (its gates in circuit order) on an n-qubit state.
 hs_status compile_part(int n, const std::vector<Gate>& part_gates, const CompileOptions& opt,
                        CompiledPart* out);
@@ -210,6 +215,8 @@ struct Plan {
   std::vector<CompiledPart> comp[2];    // for the interpreter kernel
   bool scompiled[2] = {false, false};
   std::vector<CompiledPart> scomp[2];   // for the specialized kernels
+  std::vector<Gate> reduced;            // reduce_gates(gates) and its DAG, made when
+  Dag reduced_dag;                      // first cut into sweeps or dense pieces
   SweepSet sweeps[2][2];                // [specialized][dtype]
   // uploaded descriptors and built kernels per device: [0] of the parts,
   // [1] of the sweeps

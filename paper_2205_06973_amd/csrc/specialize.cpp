@@ -192,15 +192,27 @@ void emit_op(Emit& E, const HostOp& op) {
   }
 }
 
-// Global index contributed by the lane and wave bits of layout e.
+// Whether a lane's byte offset in layout e fits 32 bits.  The loads and stores
+// then take a uniform 64-bit base, formed on the scalar unit, and the lane's
+// 32-bit offset; otherwise every access adds 64-bit addresses in vector
+// registers (two instructions and two registers each).
+bool short_lanes(const StageDesc& e, const PartDesc& d, bool f32) {
+  int top = 0;
+  for (int c = 0; c < d.lb; ++c) top = std::max(top, (int)d.tq[e.pos[c]]);
+  return top + (f32 ? 3 : 4) < 31;
+}
+
+// Global offsets of the lane bits (in bytes) and the wave bits (in amplitudes)
+// of layout e.
 void emit_thread_offsets(Emit& E, const StageDesc& e, const PartDesc& d, const char* lane_var,
                          const char* wave_var, const char* out_lane, const char* out_wave) {
   auto& o = E.o;
-  // 64-bit: lanes may carry any tile qubit (up to n - 1)
-  o << "    const unsigned long long " << out_lane << " = 0ull";
+  // 64-bit where lanes carry a high qubit (up to n - 1)
+  const std::string U = short_lanes(e, d, E.f32) ? "unsigned" : "unsigned long long";
+  o << "    const " << U << " " << out_lane << " = 0u";
   for (int c = 0; c < d.lb; ++c)
-    o << " | ((unsigned long long)((" << lane_var << " >> " << c << ") & 1u) << "
-      << (int)d.tq[e.pos[c]] << ")";
+    o << " | ((" << U << ")((" << lane_var << " >> " << c << ") & 1u) << "
+      << (int)d.tq[e.pos[c]] + (E.f32 ? 3 : 4) << ")";
   o << ";\n    const unsigned long long " << out_wave << " = 0ull";
   for (int c = 0; c < d.wb; ++c)
     o << " | ((unsigned long long)((" << wave_var << " >> " << c << ") & 1u) << "
@@ -208,8 +220,10 @@ void emit_thread_offsets(Emit& E, const StageDesc& e, const PartDesc& d, const c
   o << ";\n";
 }
 
+// Loads or stores of all registers; `base` points to the tile's (and wave's)
+// first amplitude, `lane` is the lane's byte offset.
 void emit_io(Emit& E, const StageDesc& e, const PartDesc& d, bool store, const char* prefix,
-             const char* base) {
+             const char* base, const char* lane) {
   auto& o = E.o;
   const int N = 1 << E.rb;
   for (int j = 0; j < N; ++j) {
@@ -218,10 +232,11 @@ void emit_io(Emit& E, const StageDesc& e, const PartDesc& d, bool store, const c
     for (int i = 0; i < d.m; ++i)
       if (t >> i & 1) g |= uint64_t(1) << d.tq[i];
     if (store)
-      o << "      " << base << "[" << g << "ull] = make_v(ar" << j << ", ai" << j << ");\n";
+      o << "      *(V*)((char*)(" << base << " + " << g << "ull) + " << lane << ") = make_v(ar" << j << ", ai" << j
+        << ");\n";
     else
-      o << "      { const V v = " << base << "[" << g << "ull]; " << prefix << "r" << j << " = v.x; "
-        << prefix << "i" << j << " = v.y; }\n";
+      o << "      { const V v = *(const V*)((const char*)(" << base << " + " << g << "ull) + " << lane << "); "
+        << prefix << "r" << j << " = v.x; " << prefix << "i" << j << " = v.y; }\n";
   }
 }
 
@@ -275,6 +290,27 @@ void emit_transition(Emit& E, const StageDesc& from, const StageDesc& to, const 
         o << " | (((thr >> " << c << ") & 1u) << " << cpos(e.pos[c]) << ")";
     o << ");\n";
   };
+  // The swizzle folds the higher bits of an index into its low `sw` bits, and
+  // a register's own bits above those are disjoint from the thread's: slot
+  // (thread ^ register) = (thread slot ^ low bits of the register's slot) + its
+  // high bits.  One exclusive or for each of the few low parts, the high part
+  // in the instruction's offset, instead of one address a register.
+  const uint32_t low = (1u << sw) - 1u;
+  auto reg_slot = [&](const StageDesc& e, int j) {
+    return slot(compress(reg_tile_offset(e, d.lb, d.wb, E.rb, j), sb), sw);
+  };
+  auto low_parts = [&](const StageDesc& e, const char* name) {
+    uint32_t seen = 0;
+    for (int j = 0; j < N; ++j) {
+      const uint32_t x = reg_slot(e, j) & low;
+      if (!(seen >> x & 1)) o << "    const unsigned " << name << x << " = " << name << " ^ " << x << "u;\n";
+      seen |= 1u << x;
+    }
+  };
+  auto address = [&](const StageDesc& e, const char* name, int j) {
+    const uint32_t x = reg_slot(e, j);
+    return std::string(name) + std::to_string(x & low) + " + " + std::to_string(x & ~low) + "u";
+  };
   // condition on this thread's coordinates for round h ("" = always)
   auto thread_cond = [&](const StageDesc& e, int h) {
     std::string c;
@@ -295,6 +331,8 @@ void emit_transition(Emit& E, const StageDesc& from, const StageDesc& to, const 
   o << "    {\n";
   thread_slot(from, "wb_");
   thread_slot(to, "rb_");
+  low_parts(from, "wb_");
+  low_parts(to, "rb_");
   // split rounds read into their own temporaries (s*), never into the
   // prefetch registers (n*) that hold the next tile's amplitudes
   const std::string dst = sb.empty() ? "a" : "s";
@@ -305,16 +343,13 @@ void emit_transition(Emit& E, const StageDesc& from, const StageDesc& to, const 
     o << "    if (" << (wc.empty() ? "true" : wc) << ") {\n";
     for (int j = 0; j < N; ++j)
       if (reg_in_round(from, j, h))
-        o << "      lds[wb_ ^ " << slot(compress(reg_tile_offset(from, d.lb, d.wb, E.rb, j), sb), sw)
-          << "u] = make_v(ar" << j << ", ai" << j << ");\n";
+        o << "      lds[" << address(from, "wb_", j) << "] = make_v(ar" << j << ", ai" << j << ");\n";
     o << "    }\n    __syncthreads();\n";
     const std::string rc = thread_cond(to, h);
     o << "    if (" << (rc.empty() ? "true" : rc) << ") {\n";
     for (int j = 0; j < N; ++j)
       if (reg_in_round(to, j, h))
-        o << "      { const V v = lds[rb_ ^ "
-          << slot(compress(reg_tile_offset(to, d.lb, d.wb, E.rb, j), sb), sw) << "u]; " << dst << "r"
-          << j << " = v.x; " << dst << "i" << j << " = v.y; }\n";
+        o << "      { const V v = lds[" << address(to, "rb_", j) << "]; " << dst << "r" << j << " = v.x; " << dst << "i" << j << " = v.y; }\n";
     o << "    }\n";
   }
   if (!sb.empty())
@@ -391,8 +426,8 @@ std::string specialize_part_source(const CompiledPart& cp, hs_dtype dt, const st
     << "  }\n";
   if (pf) {
     o << "  if (tile < end && active) {\n"
-      << "    const V* p = st + base_of(tile) + wo_ld + lo_ld;\n";
-    emit_io(E, cp.stages[0], d, false, "a", "p");
+      << "    const V* p = st + base_of(tile) + wo_ld;\n";
+    emit_io(E, cp.stages[0], d, false, "a", "p", "lo_ld");
     o << "  }\n";
   }
   o << "  for (; tile < end; tile += step) {\n"
@@ -400,13 +435,13 @@ std::string specialize_part_source(const CompiledPart& cp, hs_dtype dt, const st
   if (pf) {
     o << "    const unsigned long long nt = tile + step;\n"
       << "    if (nt < end && active) {\n"
-      << "      const V* p = st + base_of(nt) + wo_ld + lo_ld;\n";
-    emit_io(E, cp.stages[0], d, false, "n", "p");
+      << "      const V* p = st + base_of(nt) + wo_ld;\n";
+    emit_io(E, cp.stages[0], d, false, "n", "p", "lo_ld");
     o << "    }\n";
   } else {
     o << "    if (active) {\n"
-      << "      const V* p = st + tb + wo_ld + lo_ld;\n";
-    emit_io(E, cp.stages[0], d, false, "a", "p");
+      << "      const V* p = st + tb + wo_ld;\n";
+    emit_io(E, cp.stages[0], d, false, "a", "p", "lo_ld");
     o << "    }\n";
   }
   for (int s = 1; s < ne; ++s) {
@@ -415,8 +450,8 @@ std::string specialize_part_source(const CompiledPart& cp, hs_dtype dt, const st
     for (int i = e.op_begin; i < e.op_end; ++i) emit_op(E, cp.ops[i]);
   }
   o << "    if (active) {\n"
-    << "      V* p = st + tb + wo_st + lo_st;\n";
-  emit_io(E, cp.stages[ne - 1], d, true, "a", "p");
+    << "      V* p = st + tb + wo_st;\n";
+  emit_io(E, cp.stages[ne - 1], d, true, "a", "p", "lo_st");
   o << "    }\n";
   if (pf)
     for (int j = 0; j < N; ++j) o << "    ar" << j << " = nr" << j << "; ai" << j << " = ni" << j << ";\n";

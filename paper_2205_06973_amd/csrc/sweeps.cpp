@@ -24,9 +24,8 @@ namespace {
 
 // Tile widths to try.  Wide states: 13 qubits (complex64) or 12 (complex128)
 // leave two to five workgroups on a CU, so that the loads of one tile overlap
-// the arithmetic of another; one qubit more takes the whole CU and pays only
-// where it saves enough sweeps (random circuit on 30 qubits complex64, 13 / 14:
-// 33 sweeps of 3.46 ms, 29 of 4.02; 32-qubit QFT: 21 and 16 sweeps).  Small
+// the arithmetic of another; one qubit more hardly overlaps and pays only
+// where it saves enough sweeps and they compute little (see tile_cost).  Small
 // states: a narrower tile, so that there are tiles for the 256 CUs (layered
 // circuit on 17 qubits complex128, tiles of 13 / 12 / 11: 99 / 75 / 68 us).
 // The interpreter is bound by its instructions, not by the sweeps, and loses
@@ -42,8 +41,22 @@ std::vector<int> tile_widths(int n, hs_dtype dtype, bool spec, const CompileOpti
   return out;
 }
 
-// Relative cost of a sweep over m-qubit tiles (see tile_widths).
-double tile_cost(int m, hs_dtype dtype) { return m >= (dtype == HS_C64 ? 14 : 13) ? 1.16 : 1.0; }
+// Cost of a sweep over m-qubit tiles in HBM sweeps, `work` vector instructions
+// an amplitude in it.  Measured on 28 and 30 qubits: complex64, tiles of 13 / 14
+// qubits, 1.08 / 1.24 at 24 instructions (random circuit) and 1.38 / 1.81 at 116
+// / 132 (layered); complex128, 12 / 13 qubits, 1.05 / 1.15 and 1.31 / 1.73.
+double tile_cost(int m, hs_dtype dtype, double work) {
+  const double alu = 0.007 * work;
+  if (dtype == HS_C64) return m >= 14 ? 1.12 + 0.75 * alu : 1.02 + 0.43 * alu;
+  return m >= 13 ? 1.05 + 0.65 * alu : 1.0 + 0.33 * alu;
+}
+
+// The plan's reduced gates (p->mu held).
+void reduce_plan(Plan* p) {
+  if (!p->reduced.empty()) return;
+  p->reduced = reduce_gates(p->n, p->gates);
+  p->reduced_dag = build_dag(p->reduced);
+}
 
 // A plan keeps its parts unless regrouping takes at least a tenth of the
 // sweeps away: the wider tiles have one or two LDS re-layouts more (3% of a
@@ -63,33 +76,37 @@ hs_status plan_sweeps(Plan* p, hs_dtype dtype, bool spec, const SweepSet** out) 
   for (uint64_t mask : p->masks) parts_fit &= part_fits(p->n, mask, opt);
   opt.contig = dtype == HS_C64 ? 4 : 3;
   const uint64_t pad = (uint64_t(1) << std::min(opt.contig, p->n)) - 1;
+  if (parts_fit) reduce_plan(p);
+  const std::vector<Gate>& gates = p->reduced;
+  const Dag& dag = p->reduced_dag;
   std::vector<int32_t> best, part;
   int count = 0;
-  double cost = kWorthwhile * (double)p->parts.size();
-  // The plain closure rule chooses the width; kernels that are built for many
-  // runs get the beam search on top: 5-10% fewer sweeps at width 4 (10-14 ms
-  // per 1,000 gates) and up to 3% fewer again at 16 (20-30 ms), which a sweep
-  // of 16 GiB and more repays in one run.
-  int width = 0;
+  double work = 0;  // a matrix gate is 4 instructions an amplitude (compile.cpp), a phase on a quarter 1
+  for (const Gate& g : gates) work += g.kind == kMatrixGate ? 4 : g.kind == HS_CP ? 1 : 0;
+  double cost = 1e30;
+  // The interpreter's plans, often run once, are cut by the plain closure rule
+  // (1 ms per 1,000 gates); kernels that are built for many runs get the beam
+  // search: 8-12% fewer sweeps at width 4 (10 ms per 1,000 gates of the random
+  // circuit) and 3% fewer again at 16 (20 ms), which sweeps of 2 GiB and more
+  // repay in a few runs.
+  const int beam = !spec ? 1 : p->n >= 28 ? 16 : 4;
   if (parts_fit)
     for (int m : tile_widths(p->n, dtype, spec, opt)) {
       bool fits = true;
-      for (const Gate& g : p->gates) fits &= __builtin_popcountll(g.mask() | pad) <= m;
+      for (const Gate& g : gates) fits &= __builtin_popcountll(g.mask() | pad) <= m;
       if (!fits) continue;
-      const int c = partition_closure(p->gates, p->dag, m, 1, &part, pad);
-      if (c * tile_cost(m, dtype) < cost) {
-        cost = c * tile_cost(m, dtype);
+      const int c = partition_closure(gates, dag, m, beam, &part, pad);
+      if (c <= kWorthwhile * (double)p->parts.size() && c * tile_cost(m, dtype, work / c) < cost) {
+        cost = c * tile_cost(m, dtype, work / c);
         count = c;
-        width = m;
         best.swap(part);
       }
     }
-  if (count && spec) count = partition_closure(p->gates, p->dag, width, p->n >= 31 ? 16 : 4, &best, pad);
-  std::vector<std::vector<Gate>> gates(count);
-  for (size_t i = 0; count && i < p->gates.size(); ++i) gates[best[i]].push_back(p->gates[i]);
+  std::vector<std::vector<Gate>> piece(count);
+  for (size_t i = 0; count && i < gates.size(); ++i) piece[best[i]].push_back(gates[i]);
   std::vector<CompiledPart> comp(count);
   for (int i = 0; i < count; ++i) {
-    if (hs_status rc = compile_part(p->n, gates[i], opt, &comp[i])) return rc;
+    if (hs_status rc = compile_part(p->n, piece[i], opt, &comp[i])) return rc;
     comp[i].launch = opt.launch;
   }
   set.comp.swap(comp);
@@ -110,19 +127,20 @@ hs_status plan_fused_set(Plan* p, hs_dtype dtype, bool build, const FusedSet** o
     double cost = 0;
     for (uint64_t mask : p->masks) cost += fused_part_cost(p->n, mask, dtype);
     cost *= kWorthwhile;
-    std::vector<int32_t> best, part;
-    for (int w = 5; w <= kMaxFusedQubits && p->n >= w + 4 && cost < 1e29; ++w) {
-      const int c = partition_closure(p->gates, p->dag, w, 1, &part);
+    constexpr int w = 6;
+    std::vector<int32_t> part;
+    if (p->n >= w + 4 && cost < 1e29) {
+      reduce_plan(p);
+      const std::vector<Gate>& gates = p->reduced;
+      const int c = partition_closure(gates, p->reduced_dag, w, 1, &part);
       std::vector<uint64_t> masks(c, 0);
-      for (size_t i = 0; i < p->gates.size(); ++i) masks[part[i]] |= p->gates[i].mask();
-      double sum = 0;
-      for (uint64_t mask : masks) sum += fused_part_cost(p->n, mask, dtype);
-      if (sum >= cost) continue;
-      cost = set.cost = sum;
-      best.swap(part);
-      set.gates.assign(c, {});
+      for (size_t i = 0; i < gates.size(); ++i) masks[part[i]] |= gates[i].mask();
+      for (uint64_t mask : masks) set.cost += fused_part_cost(p->n, mask, dtype);
+      if (set.cost < cost) {
+        set.gates.assign(c, {});
+        for (size_t i = 0; i < gates.size(); ++i) set.gates[part[i]].push_back(gates[i]);
+      }
     }
-    for (size_t i = 0; i < best.size(); ++i) set.gates[best[i]].push_back(p->gates[i]);
     set.ready = true;
   }
   if (!build || set.built) return HS_OK;
