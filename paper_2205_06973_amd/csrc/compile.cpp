@@ -97,6 +97,30 @@ bool same_layout(const Layout& a, const Layout& b, int m) {
 
 bool is_exact(const cd& z, double re, double im) { return z.real() == re && z.imag() == im; }
 
+// Pending runs and their splits are kept in extended precision, so that a
+// coefficient is rounded to FP64 once, when its op is made, however many gates
+// and splits it comes from (layered circuit on 25 qubits complex128, error
+// against FP64 arithmetic: 5.9e-15 with FP64 runs, 2.5e-15 with plain gates).
+using cl = std::complex<long double>;
+
+cd to_cd(const cl& z) { return cd((double)z.real(), (double)z.imag()); }
+
+// products and reciprocals written out: the operators of std::complex also
+// order out NaNs and overflow, at ten times the cost
+cl mul(const cl& a, const cl& b) {
+  return cl(a.real() * b.real() - a.imag() * b.imag(), a.real() * b.imag() + a.imag() * b.real());
+}
+cl inv(const cl& a) {
+  const long double s = 1 / (a.real() * a.real() + a.imag() * a.imag());
+  return cl(a.real() * s, -a.imag() * s);
+}
+
+void matmul2(const cl a[4], const cl b[4], cl out[4]) {  // out = a * b
+  const cl r[4] = {mul(a[0], b[0]) + mul(a[1], b[2]), mul(a[0], b[1]) + mul(a[1], b[3]),
+                   mul(a[2], b[0]) + mul(a[3], b[2]), mul(a[2], b[1]) + mul(a[3], b[3])};
+  for (int i = 0; i < 4; ++i) out[i] = r[i];
+}
+
 void matmul2(const cd a[4], const cd b[4], cd out[4]) {  // out = a * b
   cd r[4];
   r[0] = a[0] * b[0] + a[1] * b[2];
@@ -165,100 +189,103 @@ constexpr double kMaxGrowth = 1024.0;
 
 enum Role { kRoleZ, kRoleX, kRoleLast };  // kRoleLast: nothing may stay pending
 
-// The parts of a coefficient that are rounding noise of its computation (a
-// few units in the last place of its modulus) are set to zero, so that
-// products such as RZ H keep the real form of H.
-cd clean(const cd& z) {
-  constexpr double eps = 4.5e-16;
-  double re = z.real(), im = z.imag();
-  const double mag = std::max(std::fabs(re), std::fabs(im));
+// The parts of a coefficient that are rounding noise of its computation in
+// extended precision (a tenth of FP64's) are set to zero, so that products such
+// as RZ H keep the real form of H.
+cl clean(const cl& z) {
+  constexpr long double eps = 1e-17L;
+  long double re = z.real(), im = z.imag();
+  const long double mag = std::max(std::fabs(re), std::fabs(im));
   if (std::fabs(re) <= eps * mag) re = 0;
   if (std::fabs(im) <= eps * mag) im = 0;
-  if (im == 0 && std::fabs(std::fabs(re) - 1.0) <= eps) re = std::copysign(1.0, re);
-  if (re == 0 && std::fabs(std::fabs(im) - 1.0) <= eps) im = std::copysign(1.0, im);
-  return cd(re, im);
+  if (im == 0 && std::fabs(std::fabs(re) - 1) <= eps) re = std::copysign(1.0L, re);
+  if (re == 0 && std::fabs(std::fabs(im) - 1) <= eps) im = std::copysign(1.0L, im);
+  return cl(re, im);
 }
 
 // Vector instructions a pair of amplitudes (real and imaginary parts) for
 // y = K x when every term is written out.
-int pair_cost(const cd k[4]) {
+template <typename C>
+int pair_cost(const C k[4]) {
   int c = 0;
   for (int r = 0; r < 2; ++r) {
     int terms = 0;
     bool unit = false;
     for (int i = 0; i < 2; ++i) {
-      const cd& z = k[2 * r + i];
-      if (z == cd(0, 0)) continue;
+      const C& z = k[2 * r + i];
+      if (z == C(0, 0)) continue;
       terms += (z.real() != 0 && z.imag() != 0) ? 4 : 2;
-      unit |= std::fabs(z.real()) + std::fabs(z.imag()) == 1.0;
+      unit |= std::fabs(z.real()) + std::fabs(z.imag()) == 1;
     }
     c += terms - (unit ? 2 : 0);
   }
   return c;
 }
 
-bool is_identity(const cd k[4]) {
-  return k[0] == cd(1, 0) && k[3] == cd(1, 0) && k[1] == cd(0, 0) && k[2] == cd(0, 0);
+bool is_identity(const cl k[4]) {
+  return k[0] == cl(1, 0) && k[3] == cl(1, 0) && k[1] == cl(0, 0) && k[2] == cl(0, 0);
 }
 
 struct Split {
-  cd S = 1, K[4] = {1, 0, 0, 1}, L[4] = {1, 0, 0, 1};
+  cl S = 1, K[4] = {1, 0, 0, 1}, L[4] = {1, 0, 0, 1};
   int cost = 0;        // pair_cost(K)
   double rank = 1e30;  // what the candidates are compared by
 };
 
 // M = S L K with L allowed by `role`; the cheapest of a few candidates.
-Split split_gate(const cd M[4], Role role) {
+Split split_gate(const cl M[4], Role role) {
   // scale: M may be a unitary times a number
-  const double unit = std::max(std::abs(M[0]), std::abs(M[1]));
+  const long double unit = std::max(std::abs(M[0]), std::abs(M[1]));
   if (!(unit > 0)) {
     Split whole;
     std::copy(M, M + 4, whole.K);
     whole.cost = pair_cost(M);
     return whole;
   }
-  const cd a = M[0] / unit, b = M[1] / unit, c = M[2] / unit, d = M[3] / unit, zero(0, 0);
+  const long double iu = 1 / unit;
+  const cl a = M[0] * iu, b = M[1] * iu, c = M[2] * iu, d = M[3] * iu, zero(0, 0);
   Split best;
-  auto offer = [&](cd S, cd l0, cd l1, cd l2, cd l3, cd k0, cd k1, cd k2, cd k3) {
+  auto offer = [&](cl S, cl l0, cl l1, cl l2, cl l3, cl k0, cl k1, cl k2, cl k3) {
     Split s;
     s.S = S;
-    const cd l[4] = {l0, l1, l2, l3}, k[4] = {k0, k1, k2, k3};
+    const cl l[4] = {l0, l1, l2, l3}, k[4] = {k0, k1, k2, k3};
     for (int i = 0; i < 4; ++i) {
       s.L[i] = clean(l[i]);
       s.K[i] = clean(k[i]);
     }
     s.cost = is_identity(s.K) ? 0 : pair_cost(s.K);
     // a factor left pending may have to run later (up to 4); growth 1/|S|
-    s.rank = s.cost + (is_identity(s.L) ? 0.0 : 1.0) - 0.5 * std::log2(std::min(1.0, std::abs(S)));
+    s.rank = s.cost + (is_identity(s.L) ? 0.0 : 1.0) - 0.5 * std::log2(std::min(1.0, (double)std::abs(S)));
     if (s.rank < best.rank) best = s;
   };
   const bool diag = b == zero && c == zero, anti = a == zero && d == zero;
-  const double na = std::abs(a), nb = std::abs(b);
-  constexpr double kSmall = 0.125;
+  const long double na = std::abs(a), nb = std::abs(b);
+  constexpr long double kSmall = 0.125;
   // nothing pending: M over one of its entries
-  if (na >= kSmall) offer(a, 1, 0, 0, 1, 1, b / a, c / a, d / a);
-  if (nb >= kSmall) offer(b, 1, 0, 0, 1, a / b, 1, c / b, d / b);
+  const cl ia = na >= kSmall ? inv(a) : zero, ib = nb >= kSmall ? inv(b) : zero;
+  if (na >= kSmall) offer(a, 1, 0, 0, 1, 1, mul(b, ia), mul(c, ia), mul(d, ia));
+  if (nb >= kSmall) offer(b, 1, 0, 0, 1, mul(a, ib), 1, mul(c, ib), mul(d, ib));
   if (role == kRoleZ) {
-    if (diag) offer(a, 1, 0, 0, d / a, 1, 0, 0, 1);
-    else if (anti) offer(b, 1, 0, 0, c / b, 0, 1, 1, 0);
+    if (diag) offer(a, 1, 0, 0, mul(d, ia), 1, 0, 0, 1);
+    else if (anti) offer(b, 1, 0, 0, mul(c, ib), 0, 1, 1, 0);
     else {
-      if (na >= kSmall) offer(a, 1, 0, 0, d / a, 1, b / a, c / d, 1);
-      if (nb >= kSmall) offer(b, 1, 0, 0, c / b, a / b, 1, 1, d / c);
+      if (na >= kSmall) offer(a, 1, 0, 0, mul(d, ia), 1, mul(b, ia), mul(c, inv(d)), 1);
+      if (nb >= kSmall) offer(b, 1, 0, 0, mul(c, ib), mul(a, ib), 1, 1, mul(d, inv(c)));
     }
   } else if (role == kRoleX) {
     // M = e^{ig} (w - i (x X + y Y + z Z)); L = cos t - i sin t X with
     // tan t = z / y leaves K without a Z component: [[w', -y'-ix'], [y'-ix', w']]
-    const cd ph = std::sqrt(a * d - b * c);
-    const cd u0 = a / ph, u1 = b / ph;
-    const double w = u0.real(), z = -u0.imag(), y = -u1.real(), x = -u1.imag();
-    const double r = std::hypot(y, z);
-    if (r <= 4.5e-16) {
-      offer(ph, cd(w, 0), cd(0, -x), cd(0, -x), cd(w, 0), 1, 0, 0, 1);
+    const cl ph = std::sqrt(mul(a, d) - mul(b, c));
+    const cl ip = inv(ph), u0 = mul(a, ip), u1 = mul(b, ip);
+    const long double w = u0.real(), z = -u0.imag(), y = -u1.real(), x = -u1.imag();
+    const long double r = std::hypot(y, z);
+    if (r <= 1e-18L) {
+      offer(ph, cl(w, 0), cl(0, -x), cl(0, -x), cl(w, 0), 1, 0, 0, 1);
     } else {
-      const double ct = y / r, sn = z / r;
-      const double w1 = w * ct + sn * x, x1 = x * ct - sn * w, y1 = r;
+      const long double ct = y / r, sn = z / r;
+      const long double w1 = w * ct + sn * x, x1 = x * ct - sn * w, y1 = r;
       if (std::fabs(w1) >= kSmall)
-        offer(ph * w1, cd(ct, 0), cd(0, -sn), cd(0, -sn), cd(ct, 0), 1, cd(-y1, -x1) / w1, cd(y1, -x1) / w1, 1);
+        offer(ph * w1, cl(ct, 0), cl(0, -sn), cl(0, -sn), cl(ct, 0), 1, cl(-y1, -x1) / w1, cl(y1, -x1) / w1, 1);
     }
   }
   best.S *= unit;
@@ -277,34 +304,35 @@ Split split_gate(const cd M[4], Role role) {
 std::vector<Gate> reduce_gates(int n, const std::vector<Gate>& gates) {
   std::vector<Gate> out;
   out.reserve(gates.size());
-  std::vector<std::array<cd, 4>> pend(n);
+  std::vector<std::array<cl, 4>> pend(n);
   std::vector<char> has(n, 0);
-  cd phase = 1;
+  cl phase = 1;
   int last = -1;  // a matrix gate to carry the phase
-  auto put = [&](int q, const cd u[4]) {
+  auto put = [&](int q, const cl u[4]) {
     Gate g{};
     g.kind = kMatrixGate;
     g.q0 = q;
     g.q1 = -1;
-    std::copy(u, u + 4, g.u);
+    for (int i = 0; i < 4; ++i) g.u[i] = to_cd(u[i]);
     last = (int)out.size();
     out.push_back(g);
   };
   auto flush = [&](int q, Role role) {
     if (!has[q]) return;
     Split f = split_gate(pend[q].data(), role);
-    const double mag = std::abs(f.S);
-    phase *= f.S / mag;
+    const long double mag = std::abs(f.S);
+    phase = mul(phase, f.S / mag);
     std::copy(f.L, f.L + 4, pend[q].begin());
     has[q] = !is_identity(f.L);
     if (is_identity(f.K)) return;
-    for (cd& z : f.K) z *= mag;
+    for (cl& z : f.K) z *= mag;
     put(q, f.K);
   };
   for (const Gate& g : gates) {
     if (g.arity() == 1) {
-      cd u[4];
-      gate_matrix(g, u);
+      cd m[4];
+      gate_matrix(g, m);
+      const cl u[4] = {m[0], m[1], m[2], m[3]};
       if (has[g.q0]) matmul2(u, pend[g.q0].data(), pend[g.q0].data());
       else std::copy(u, u + 4, pend[g.q0].begin());
       has[g.q0] = 1;
@@ -320,11 +348,11 @@ std::vector<Gate> reduce_gates(int n, const std::vector<Gate>& gates) {
     out.push_back(g);
   }
   for (int q = 0; q < n; ++q) flush(q, kRoleLast);
-  if (clean(phase) != cd(1, 0)) {
-    const cd d[4] = {phase, 0, 0, phase};
+  if (clean(phase) != cl(1, 0)) {
+    const cl d[4] = {phase, 0, 0, phase};
     if (last < 0) put(0, d);
     else
-      for (cd& z : out[last].u) z *= phase;
+      for (cd& z : out[last].u) z = to_cd(cl(z) * phase);
   }
   return out;
 }
@@ -464,22 +492,22 @@ void u2_apply_after(HostOp* op, int r0, const cd m[16]) {
 // Multiply the part's scalar S into the op where that adds the fewest
 // instructions (a dense 4 x 4 takes it for nothing, diag(1, d) costs the
 // other half of the amplitudes), or append it as a diagonal.
-void fold_scalar(const cd& S, std::vector<HostOp>* ops) {
-  if (clean(S) == cd(1, 0)) return;
+void fold_scalar(const cl& S, std::vector<HostOp>* ops) {
+  if (clean(S) == cl(1, 0)) return;
   int at = -1, cost = 8;  // a diagonal of its own: 8 instructions a pair
-  cd k[4], best[4] = {S, 0, 0, S};
+  cd k[4], best[4] = {to_cd(S), 0, 0, to_cd(S)};
   for (int i = 0; i < (int)ops->size(); ++i) {
     HostOp& op = (*ops)[i];
     if (op.kind == OP_U2) {
       cd m[16];
       get_u2(op, m);
-      for (cd& z : m) z *= S;
+      for (cd& z : m) z = to_cd(cl(z) * S);
       set_u2(&op, m);
       return;
     }
     if (!op_matrix(op, k)) continue;
     const int before = op.kind == OP_X ? 0 : pair_cost(k);
-    for (cd& z : k) z = clean(z * S);
+    for (cd& z : k) z = to_cd(clean(cl(z) * S));
     if (pair_cost(k) - before < cost) {
       cost = pair_cost(k) - before;
       at = i;
@@ -602,14 +630,14 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
   const Layout* prev = &load;
   // One-qubit runs pending per tile bit.  A run stays pending over a change
   // of stage when a later stage has gates on its bit.
-  cd pend[kMaxTile][4];
+  cl pend[kMaxTile][4];
   bool has[kMaxTile] = {false};
   int last_stage[kMaxTile];
   for (int t = 0; t < kMaxTile; ++t) last_stage[t] = -1;
   for (size_t s = 0; s < st.size(); ++s)
     for (int t = 0; t < m; ++t)
       if (st[s].bits >> t & 1) last_stage[t] = (int)s;
-  cd scale = 1;  // the part's scalar S
+  cl scale = 1;  // the part's scalar S
   const int A = 1 << rb;
   const cd I2[4] = {1, 0, 0, 1};
   for (size_t s = 0; s < st.size(); ++s) {
@@ -624,6 +652,9 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
     int last[kMaxTile];
     for (int t = 0; t < kMaxTile; ++t) last[t] = -1;
     auto open_u2 = [&](int t) { return opt.fuse2 && last[t] >= 0 && out->ops[last[t]].kind == OP_U2; };
+    auto pending = [&](int t, cd u[4]) {
+      for (int j = 0; j < 4; ++j) u[j] = to_cd(pend[t][j]);
+    };
     // run what is pending on bit t, as far as `role` does not let it wait
     auto flush = [&](int t, Role role) {
       if (!has[t]) return;
@@ -631,29 +662,36 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
         has[t] = false;
         HostOp& o = out->ops[last[t]];
         cd m4[16];
-        kron2(reg_of[t] == o.b0 ? pend[t] : I2, reg_of[t] == o.b0 ? I2 : pend[t], m4);
+        cd run[4];
+        pending(t, run);
+        kron2(reg_of[t] == o.b0 ? run : I2, reg_of[t] == o.b0 ? I2 : run, m4);
         u2_apply_after(&o, o.b0, m4);
         return;
       }
       Split f;
       if (opt.plain) std::copy(pend[t], pend[t] + 4, f.K);
       else f = split_gate(pend[t], role);
-      scale *= f.S;
+      scale = mul(scale, f.S);
       for (int j = 0; j < 4; ++j) pend[t][j] = f.L[j];
       has[t] = !is_identity(f.L);
       if (is_identity(f.K)) return;
       if (std::abs(scale) < 1.0 / kMaxGrowth) {
-        for (cd& z : f.K) z *= scale;
+        for (cl& z : f.K) z = mul(z, scale);
         scale = 1;
       }
       const size_t before = out->ops.size();
-      emit_1q(reg_of[t], f.K, &out->ops);
+      const cd k[4] = {to_cd(f.K[0]), to_cd(f.K[1]), to_cd(f.K[2]), to_cd(f.K[3])};
+      emit_1q(reg_of[t], k, &out->ops);
       if (out->ops.size() > before) last[t] = (int)before;
     };
     // interpreter cost of what a two-qubit gate with this role makes run
     auto pend_cost = [&](int t, Role role) {
       if (!has[t] || open_u2(t)) return 0;
-      if (opt.plain) return op_cost(kind_1q(pend[t]), A, true);
+      if (opt.plain) {
+        cd run[4];
+        pending(t, run);
+        return op_cost(kind_1q(run), A, true);
+      }
       const int c = split_gate(pend[t], role).cost;
       return c ? c * A / 2 + 10 : 0;
     };
@@ -674,8 +712,14 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
       if (g.arity() == 1) {
         cd u[4];
         gate_matrix(g, u);
-        if (has[t0]) {
-          matmul2(u, pend[t0], pend[t0]);
+        if (has[t0] && opt.plain) {
+          cd run[4];
+          pending(t0, run);
+          matmul2(u, run, run);
+          for (int j = 0; j < 4; ++j) pend[t0][j] = run[j];
+        } else if (has[t0]) {
+          const cl v[4] = {u[0], u[1], u[2], u[3]};
+          matmul2(v, pend[t0], pend[t0]);
         } else {
           for (int j = 0; j < 4; ++j) pend[t0][j] = u[j];
           has[t0] = true;
@@ -687,7 +731,10 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
       if (opt.fuse2) {
         cd m4[16], pm[16];
         if (hs_status rc = gate4(g, m4)) return rc;
-        kron2(has[t0] ? pend[t0] : I2, has[t1] ? pend[t1] : I2, pm);
+        cd run0[4], run1[4];
+        pending(t0, run0);
+        pending(t1, run1);
+        kron2(has[t0] ? run0 : I2, has[t1] ? run1 : I2, pm);
         matmul4(m4, pm, m4);  // the pending one-qubit gates come first
         const int r0 = reg_of[t0], r1 = reg_of[t1];
         const int gk = g.kind == HS_CX ? OP_CX : g.kind == HS_CZ ? OP_CZ : g.kind == HS_CP ? OP_CP : OP_SWAP;
