@@ -376,6 +376,9 @@ double op_work(const HostOp& op) {
     case OP_D1: return 2;
     case OP_CP: return 1;
     case OP_U2: return 16;
+    case OP_CPC: case OP_CXC: return 2;
+    case OP_FA: return op.b0 ? 2 : 4;
+    case OP_GA: return op.b1 ? 1 : 2;
     default: return 0;  // permutations and sign changes
   }
 }
@@ -535,8 +538,11 @@ bool part_fits(int n, uint64_t mask, const CompileOptions& opt) {
 hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions& opt,
                        CompiledPart* out) {
   if (pg.empty()) return fail(HS_E_ARG, "empty part");
+  // what the gates need in the tile, and in the registers of their stage
+  const std::vector<Gate> stand_ins = opt.conditions ? active_gates(pg) : std::vector<Gate>();
+  const std::vector<Gate>& act = opt.conditions ? stand_ins : pg;
   uint64_t S = 0;
-  for (const Gate& g : pg) S |= g.mask();
+  for (const Gate& g : act) S |= g.mask();
   const int C = std::min(opt.contig, n);
   const uint64_t need = S | ((C >= 64) ? ~0ull : ((1ull << C) - 1));
   int m = std::max(__builtin_popcountll(need),
@@ -573,23 +579,19 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
     uint32_t bits = 0;
     std::vector<int> gates;
   };
-  for (const Gate& g : pg)
+  for (const Gate& g : act)
     if (g.arity() > rb) return fail(HS_E_UNSUPPORTED, "gate wider than the register stage");
   std::vector<int32_t> stage_of, greedy_of;
-  const Dag pdag = build_dag(pg);
-  int nst = partition_dfs(pg, pdag, rb, kStageSeed, kStageTrials, &stage_of);
-  const int ngr = partition_greedy(pg, pdag, rb, kStageSeed, kStageTrials, &greedy_of);
+  const Dag pdag = opt.conditions ? commuting_dag(n, pg) : build_dag(pg);
+  int nst = partition_dfs(act, pdag, rb, kStageSeed, kStageTrials, &stage_of);
+  const int ngr = partition_greedy(act, pdag, rb, kStageSeed, kStageTrials, &greedy_of);
   if (ngr < nst) {
     nst = ngr;
     stage_of.swap(greedy_of);
   }
   std::vector<Stage> st(nst);
-  for (int i = 0; i < (int)pg.size(); ++i) {
-    Stage& S = st[stage_of[i]];
-    S.bits |= 1u << bit_of[pg[i].q0];
-    if (pg[i].q1 >= 0) S.bits |= 1u << bit_of[pg[i].q1];
-    S.gates.push_back(i);
-  }
+  for (int i = 0; i < (int)pg.size(); ++i)
+    for (uint64_t qs = act[i].mask(); qs; qs &= qs - 1) st[stage_of[i]].bits |= 1u << bit_of[__builtin_ctzll(qs)];
 
   out->desc = PartDesc{};
   out->desc.m = m;
@@ -609,6 +611,25 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
     lay.push_back(make_layout(m, lb, wb, regs));
     prev_regs = regs;
   }
+  auto is_reg = [&](int q, int s) {
+    for (int r = 0; r < rb; ++r)
+      if (q >= 0 && lay[s].pos[lb + wb + r] == bit_of[q]) return true;
+    return false;
+  };
+  // A gate that needs no register bit goes to the first stage, up to those of
+  // the gates that follow it, where one of its qubits is one: it then
+  // multiplies half of the registers instead of the lane's factor.
+  for (int i = (int)pg.size() - 1; i >= 0 && opt.conditions; --i) {
+    if (act[i].mask()) continue;
+    int limit = nst - 1;
+    for (int j : pdag.succ[i]) limit = std::min(limit, (int)stage_of[j]);
+    for (int s = stage_of[i]; s <= limit; ++s)
+      if (is_reg(pg[i].q0, s) || is_reg(pg[i].q1, s)) {
+        stage_of[i] = s;
+        break;
+      }
+  }
+  for (int i = 0; i < (int)pg.size(); ++i) st[stage_of[i]].gates.push_back(i);
   // load and store layouts: lanes on tile bits 0..lb-1 (contiguous global runs)
   auto io_layout = [&](const Layout& near) {
     if (lanes_are_low(near, lb) || low_run(near, lb) >= std::min(opt.min_run, lb)) return near;
@@ -655,6 +676,30 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
     auto pending = [&](int t, cd u[4]) {
       for (int j = 0; j < 4; ++j) u[j] = to_cd(pend[t][j]);
     };
+    // Phases on a register bit under conditions commute until something mixes
+    // the bit's pairs.  They are collected until then: one is applied as it is,
+    // several are multiplied into the lane's factor (six instructions each
+    // instead of two an amplitude) and applied together.
+    std::vector<HostOp> phases[kMaxTile];
+    auto apply_phases = [&](int t) {
+      std::vector<HostOp>& ph = phases[t];
+      if (ph.empty()) return;
+      if (ph.size() == 1) {
+        out->ops.push_back(ph[0]);
+      } else {
+        HostOp all{};
+        all.kind = OP_GA;
+        all.b0 = ph[0].b0;
+        all.b1 = 1;
+        for (HostOp& op : ph) {
+          op.kind = OP_F;
+          if (op.c[1] != 0) all.b1 = 0;
+          out->ops.push_back(op);
+        }
+        out->ops.push_back(all);
+      }
+      ph.clear();
+    };
     // run what is pending on bit t, as far as `role` does not let it wait
     auto flush = [&](int t, Role role) {
       if (!has[t]) return;
@@ -680,6 +725,7 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
         scale = 1;
       }
       const size_t before = out->ops.size();
+      if (!(f.K[1] == cl(0, 0) && f.K[2] == cl(0, 0))) apply_phases(t);
       const cd k[4] = {to_cd(f.K[0]), to_cd(f.K[1]), to_cd(f.K[2]), to_cd(f.K[3])};
       emit_1q(reg_of[t], k, &out->ops);
       if (out->ops.size() > before) last[t] = (int)before;
@@ -706,9 +752,61 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
       next[o] = {upcoming[t0], upcoming[t1]};
       upcoming[t0] = upcoming[t1] = o;
     }
+    // where the value of a qubit that is no register bit is found
+    auto cond_of = [&](int q) {
+      if (bit_of[q] < 0) return kOuterBit + q;
+      int c = 0;
+      while (lay[s].pos[c] != bit_of[q]) ++c;
+      return c;
+    };
+    auto in_reg = [&](int q) { return bit_of[q] >= 0 && reg_of[bit_of[q]] >= 0; };
+    // factors of all amplitudes of a lane; they commute with everything in the
+    // stage and are applied together at its end
+    std::vector<HostOp> factors;
+    auto put_factor = [&](int cond, int cond2, const cl& d) {
+      HostOp op{};
+      op.kind = OP_F;
+      op.cond = cond;
+      op.cond2 = cond2;
+      const cd z = to_cd(clean(d));
+      op.c[0] = z.real();
+      op.c[1] = z.imag();
+      factors.push_back(op);
+    };
     for (size_t o = 0; o < st[s].gates.size(); ++o) {
       const Gate& g = pg[st[s].gates[o]];
       const int t0 = bit_of[g.q0];
+      if (opt.conditions && g.arity() == 1 && t0 < 0) {  // a diagonal on a qubit outside the tile
+        scale = mul(scale, g.u[0]);
+        put_factor(cond_of(g.q0), kNoCond, mul(g.u[3], inv(g.u[0])));
+        continue;
+      }
+      // CZ, CP or CX with a qubit that is no register bit; what is pending on
+      // that qubit is diagonal and commutes
+      if (opt.conditions && g.arity() == 2 && !(in_reg(g.q0) && in_reg(g.q1))) {
+        const cl d = g.kind == HS_CZ ? cl(-1, 0) : cl(cos(g.p[0]), sin(g.p[0]));
+        if (!in_reg(g.q0) && !in_reg(g.q1)) {
+          put_factor(cond_of(g.q0), cond_of(g.q1), d);
+          continue;
+        }
+        const int q = in_reg(g.q1) ? g.q1 : g.q0, other = q == g.q0 ? g.q1 : g.q0;
+        flush(bit_of[q], g.kind == HS_CX ? kRoleX : kRoleZ);
+        HostOp op{};
+        op.kind = g.kind == HS_CX ? OP_CXC : OP_CPC;
+        op.b0 = reg_of[bit_of[q]];
+        op.b1 = -1;
+        op.cond = cond_of(other);
+        op.cond2 = kNoCond;
+        op.c[0] = to_cd(d).real();
+        op.c[1] = to_cd(d).imag();
+        if (op.kind == OP_CPC) {
+          phases[bit_of[q]].push_back(op);
+        } else {
+          apply_phases(bit_of[q]);
+          out->ops.push_back(op);
+        }
+        continue;
+      }
       if (g.arity() == 1) {
         cd u[4];
         gate_matrix(g, u);
@@ -777,6 +875,8 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
         flush(t0, kRoleZ);
         flush(t1, role1);
       }
+      if (g.kind == HS_SWAP) apply_phases(t0);
+      if (g.kind == HS_SWAP || g.kind == HS_CX) apply_phases(t1);
       last[t0] = last[t1] = (int)out->ops.size();
       HostOp op{};
       op.b0 = reg_of[t0];
@@ -796,7 +896,31 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
     }
     for (int r = 0; r < rb; ++r) {
       const int t = lay[s].pos[lb + wb + r];
-      if (open_u2(t) || last_stage[t] <= (int)s || opt.plain) flush(t, kRoleLast);
+      const bool end = s + 1 == st.size();
+      if (opt.conditions) flush(t, end ? kRoleLast : kRoleZ);  // only diagonals wait for another stage
+      else if (open_u2(t) || last_stage[t] <= (int)s || opt.plain) flush(t, kRoleLast);
+    }
+    for (int t = 0; t < m; ++t) apply_phases(t);
+    if (s + 1 == st.size() && opt.conditions) {
+      for (int t = 0; t < m; ++t)
+        if (has[t]) {  // a diagonal on a lane or wave bit
+          scale = mul(scale, pend[t][0]);
+          put_factor(cond_of(tq[t]), kNoCond, mul(pend[t][3], inv(pend[t][0])));
+        }
+      if (!factors.empty() && clean(scale) != cl(1, 0)) {
+        put_factor(kNoCond, kNoCond, scale);
+        scale = 1;
+      }
+    }
+    if (!factors.empty()) {
+      HostOp all{};
+      all.kind = OP_FA;
+      all.b0 = 1;
+      for (const HostOp& op : factors) {
+        if (op.c[1] != 0) all.b0 = 0;
+        out->ops.push_back(op);
+      }
+      out->ops.push_back(all);
     }
     if (s + 1 == st.size()) fold_scalar(scale, &out->ops);
     out->stages.back().op_end = (int)out->ops.size();

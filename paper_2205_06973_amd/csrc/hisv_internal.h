@@ -48,8 +48,8 @@ struct Gate {
   double p[3];
   cd u[4];  // kMatrixGate only
   int arity() const { return q1 < 0 ? 1 : 2; }
-  uint64_t mask() const {
-    return (uint64_t(1) << q0) | (q1 >= 0 ? (uint64_t(1) << q1) : 0);
+  uint64_t mask() const {  // q0 < 0: a stand-in that needs no qubit (active_gates)
+    return (q0 >= 0 ? uint64_t(1) << q0 : 0) | (q1 >= 0 ? (uint64_t(1) << q1) : 0);
   }
 };
 
@@ -93,8 +93,10 @@ int partition_greedy(const std::vector<Gate>& gates, const Dag& dag, int k, uint
 int host_threads();
 // hs_tune("serve_chunk"): parts a serving request enqueues at a time.
 int serve_chunk_parts();
+// weigh_all: every gate that needs a qubit counts towards a part's weight, not
+// only those on two.
 int partition_closure(const std::vector<Gate>& gates, const Dag& dag, int k, int width,
-                      std::vector<int32_t>* part, uint64_t pad = 0);
+                      std::vector<int32_t>* part, uint64_t pad = 0, bool weigh_all = false);
 // Exact validity check; returns "" when valid, else the first violation.
 std::string check_partition(const std::vector<Gate>& gates, const Dag& dag,
                             const std::vector<int32_t>& part, int k, uint64_t pad = 0);
@@ -103,7 +105,12 @@ std::string check_partition(const std::vector<Gate>& gates, const Dag& dag,
 struct HostOp {
   int kind, b0, b1;
   double c[32];  // OP_U2: 4 x 4 complex; the others use the first 8
+  // Conditions of the OP_C* and OP_F kinds: a lane or wave coordinate bit of the
+  // stage's layout, kOuterBit + a qubit outside the tile, or kNoCond.
+  int cond, cond2;
 };
+constexpr int kNoCond = -1;
+constexpr int kOuterBit = 100;
 
 // How a part-pass grid walks the tiles of a part.  Workgroup b of a launch
 // runs on XCD b % 8 and each XCD has its own L2; the hardware sustains more
@@ -154,9 +161,21 @@ struct CompileOptions {
                      // (longer contiguous runs per tile); 0 = lanes + registers
   bool fuse2 = false;  // merge two-qubit gates with their one-qubit neighbours
                        // into dense 4 x 4 ops where that saves instructions
+  // Only the qubits a gate needs as register bits (active_gates) have to be in
+  // the tile and in a stage's registers; the others are read off the
+  // amplitude's index.  Gates are reduced ones; specialized kernels only.
+  bool conditions = false;
   bool plain = false;  // apply every one-qubit run whole, where it ends (Plan::plain)
   LaunchShape launch;
 };
+
+// Stand-ins for a circuit's gates that carry only the qubits a kernel needs in
+// its registers to apply them -- a controlled gate's target, a swap's pair,
+// none for CZ and CP, which only multiply amplitudes by a factor their index
+// selects -- and the order that really binds them: gates that act on a shared
+// qubit by its value alone, or both as a rotation about X, commute.
+std::vector<Gate> active_gates(const std::vector<Gate>& gates);
+Dag commuting_dag(int n, const std::vector<Gate>& gates);
 
 // The same circuit with its one-qubit gates as few matrices (compile.cpp).
 std::vector<Gate> reduce_gates(int n, const std::vector<Gate>& gates);

@@ -210,13 +210,13 @@ class ClosureSearch {
     bool is_placed(int i) const { return placed[i >> 6] >> (i & 63) & 1; }
   };
 
-  ClosureSearch(const std::vector<Gate>& gates, const Dag& dag, int k, uint64_t pad)
+  ClosureSearch(const std::vector<Gate>& gates, const Dag& dag, int k, uint64_t pad, bool weigh_all)
       : dag_(dag), k_(k), pad_(pad), G_(dag.G) {
     mask_.resize(G_);
     weight_.resize(G_);
     for (int i = 0; i < G_; ++i) {
       mask_[i] = gates[i].mask();
-      weight_[i] = __builtin_popcountll(mask_[i]) > 1 ? 1 : 0;
+      weight_[i] = __builtin_popcountll(mask_[i]) > (weigh_all ? 0 : 1) ? 1 : 0;
     }
     tin_.assign(G_, 0);
     tstamp_.assign(G_, 0);
@@ -428,7 +428,7 @@ class ClosureSearch {
 // plain rule (width 1) needs fewer parts.  The result does not depend on
 // the number of host threads.
 int partition_closure(const std::vector<Gate>& gates, const Dag& dag, int k, int width,
-                      std::vector<int32_t>* part, uint64_t pad) {
+                      std::vector<int32_t>* part, uint64_t pad, bool weigh_all) {
   using Node = ClosureSearch::Node;
   if (dag.G == 0) {
     part->clear();
@@ -439,7 +439,7 @@ int partition_closure(const std::vector<Gate>& gates, const Dag& dag, int k, int
   // the beam's expansions run on up to 8 host threads (hs_tune "host_threads")
   const int want = host_threads();
   const int T = std::max(1, std::min(B, want > 0 ? want : std::min(8, (int)std::thread::hardware_concurrency())));
-  std::vector<ClosureSearch> cs(T, ClosureSearch(gates, dag, k, pad));
+  std::vector<ClosureSearch> cs(T, ClosureSearch(gates, dag, k, pad, weigh_all));
   std::vector<Node> beam{cs[0].root()};
   std::vector<std::vector<Node>> grown(B);
   std::vector<std::vector<uint64_t>> qs(T);
@@ -570,7 +570,7 @@ int partition_closure(const std::vector<Gate>& gates, const Dag& dag, int k, int
   if (result < 0) return partition_nat(gates, k, part, pad);
   if (B > 1) {  // never more parts than the plain rule
     std::vector<int32_t> plain;
-    const int np = partition_closure(gates, dag, k, 1, &plain, pad);
+    const int np = partition_closure(gates, dag, k, 1, &plain, pad, weigh_all);
     if (np < result) {
       part->swap(plain);
       result = np;

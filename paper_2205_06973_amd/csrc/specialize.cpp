@@ -59,8 +59,18 @@ struct Emit {
   std::ostringstream o;
   bool f32;
   int rb;
+  int lb = 6;  // lane bits: coordinate bits below are the lane's, above the wave's
   std::string T() const { return f32 ? "float" : "double"; }
 };
+
+// The condition of an op as an expression; uniform over a wavefront unless it
+// is a lane bit.
+std::string condition(const Emit& E, int cond) {
+  if (cond >= kOuterBit) return "((tb >> " + std::to_string(cond - kOuterBit) + ") & 1ull) != 0ull";
+  if (cond >= E.lb) return "((wave >> " + std::to_string(cond - E.lb) + ") & 1u) != 0u";
+  return "((lane >> " + std::to_string(cond) + ") & 1u) != 0u";
+}
+bool uniform(const Emit& E, int cond) { return cond >= E.lb; }
 
 // One component of c0 p + c1 q (c = re, im of both; p and q given by the
 // names of their parts): terms whose coefficient is zero are left out, +-1
@@ -186,6 +196,77 @@ void emit_op(Emit& E, const HostOp& op) {
         }
         o << "  }\n";
       }
+      break;
+    }
+    case OP_CPC: {
+      const bool flip = op.c[0] == -1.0 && op.c[1] == 0.0;
+      if (uniform(E, op.cond)) {
+        o << "  if (" << condition(E, op.cond) << ") {\n";
+        for (int j = 0; j < N; ++j)
+          if (j >> op.b0 & 1) {
+            o << "  { const " << E.T() << " px = ar" << j << ", py = ai" << j << ";\n"
+              << "    ar" << j << " = " << row(op.c, "px", "py", "", "", false, f) << "; ai" << j << " = "
+              << row(op.c, "px", "py", "", "", true, f) << "; }\n";
+          }
+        o << "  }\n";
+      } else {
+        o << "  { const bool on = " << condition(E, op.cond) << "; const " << E.T() << " dr = on ? " << L(op.c[0])
+          << " : " << L(1.0);
+        if (!flip) o << ", di = on ? " << L(op.c[1]) << " : " << L(0.0);
+        o << ";\n";
+        for (int j = 0; j < N; ++j)
+          if (j >> op.b0 & 1) {
+            if (flip) o << "    ar" << j << " *= dr; ai" << j << " *= dr;\n";
+            else
+              o << "    { const " << E.T() << " px = ar" << j << ", py = ai" << j << "; ar" << j
+                << " = px*dr - py*di; ai" << j << " = px*di + py*dr; }\n";
+          }
+        o << "  }\n";
+      }
+      break;
+    }
+    case OP_CXC: {
+      // uniform: a branch around the exchange; by lane: selects
+      const bool u = uniform(E, op.cond);
+      o << (u ? "  if (" : "  { const bool on = ") << condition(E, op.cond) << (u ? ") {\n" : ";\n");
+      for (int j = 0; j < N; ++j) {
+        if (j >> op.b0 & 1) continue;
+        const int k = j | (1 << op.b0);
+        for (const char* x : {"ar", "ai"}) {
+          o << "    { const " << E.T() << " p = " << x << j << ", q = " << x << k << "; ";
+          if (u) o << x << j << " = q; " << x << k << " = p; }\n";
+          else o << x << j << " = on ? q : p; " << x << k << " = on ? p : q; }\n";
+        }
+      }
+      o << "  }\n";
+      break;
+    }
+    case OP_F: {
+      // the lane's factor fr + i fi (fi stays 0 while all factors are real)
+      std::string on;
+      if (op.cond != kNoCond) on = condition(E, op.cond);
+      if (op.cond2 != kNoCond) on += " && " + condition(E, op.cond2);
+      o << "  { const " << E.T() << " dr = " << (on.empty() ? "" : on + " ? ") << L(op.c[0])
+        << (on.empty() ? "" : " : " + L(1.0));
+      if (op.c[1] == 0.0) {
+        o << "; fr *= dr; fi *= dr; }\n";
+      } else {
+        o << ", di = " << (on.empty() ? "" : on + " ? ") << L(op.c[1]) << (on.empty() ? "" : " : " + L(0.0))
+          << ", t = fr;\n    fr = t*dr - fi*di; fi = t*di + fi*dr; }\n";
+      }
+      break;
+    }
+    case OP_FA:
+    case OP_GA: {
+      const bool real = op.kind == OP_FA ? op.b0 : op.b1;
+      for (int j = 0; j < N; ++j) {
+        if (op.kind == OP_GA && !(j >> op.b0 & 1)) continue;
+        if (real) o << "  ar" << j << " *= fr; ai" << j << " *= fr;\n";
+        else
+          o << "  { const " << E.T() << " px = ar" << j << ", py = ai" << j << "; ar" << j << " = px*fr - py*fi; ai"
+            << j << " = px*fi + py*fr; }\n";
+      }
+      o << "  fr = " << L(1.0) << "; fi = " << L(0.0) << ";\n";
       break;
     }
     default: break;
@@ -365,6 +446,7 @@ std::string specialize_part_source(const CompiledPart& cp, hs_dtype dt, const st
   E.f32 = dt == HS_C64;
   E.rb = cp.rb_kernel;
   const PartDesc& d = cp.desc;
+  E.lb = d.lb;
   const int N = 1 << E.rb;
   const int sw = E.f32 ? 4 : 3;
   const int ne = (int)cp.stages.size();
@@ -444,6 +526,9 @@ std::string specialize_part_source(const CompiledPart& cp, hs_dtype dt, const st
     emit_io(E, cp.stages[0], d, false, "a", "p", "lo_ld");
     o << "    }\n";
   }
+  bool factors = false;
+  for (const HostOp& op : cp.ops) factors |= op.kind == OP_F;
+  if (factors) o << "    " << T << " fr = " << lit(1.0, E.f32) << ", fi = " << lit(0.0, E.f32) << ";\n";
   for (int s = 1; s < ne; ++s) {
     const StageDesc& e = cp.stages[s];
     if (e.transition) emit_transition(E, cp.stages[s - 1], e, d, sw, nsplit);

@@ -65,6 +65,60 @@ constexpr double kWorthwhile = 0.9;
 
 }  // namespace
 
+std::vector<Gate> active_gates(const std::vector<Gate>& gates) {
+  std::vector<Gate> out;
+  out.reserve(gates.size());
+  for (const Gate& g : gates) {
+    Gate a{};
+    a.kind = kMatrixGate;
+    a.q0 = a.q1 = -1;
+    switch (g.kind) {
+      case HS_CZ: case HS_CP: break;
+      case HS_CX: a.q0 = g.q1; break;
+      case HS_SWAP: a.q0 = g.q0; a.q1 = g.q1; break;
+      default:
+        if (!(g.u[1] == cd(0, 0) && g.u[2] == cd(0, 0))) a.q0 = g.q0;
+    }
+    out.push_back(a);
+  }
+  return out;
+}
+
+Dag commuting_dag(int n, const std::vector<Gate>& gates) {
+  // How a gate acts on one of its qubits; gates of one class (but kOther)
+  // commute on it.
+  enum Class { kValue, kXLike, kOther };
+  struct Wire {
+    Class cls = kOther;
+    std::vector<int> group, before;  // the latest run of one class, and the one it follows
+  };
+  Dag d;
+  d.G = (int)gates.size();
+  d.succ.resize(d.G);
+  d.pred.resize(d.G);
+  std::vector<Wire> wire(n);
+  for (int i = 0; i < d.G; ++i) {
+    const Gate& g = gates[i];
+    auto visit = [&](int q, Class c) {
+      Wire& w = wire[q];
+      if (c == kOther || c != w.cls) {
+        w.before.swap(w.group);
+        w.group.clear();
+        w.cls = c;
+      }
+      w.group.push_back(i);
+      for (int b : w.before) d.pred[i].push_back(b);
+    };
+    const bool diag1 = g.arity() == 1 && g.u[1] == cd(0, 0) && g.u[2] == cd(0, 0);
+    visit(g.q0, g.kind == HS_CX || g.kind == HS_CZ || g.kind == HS_CP || diag1 ? kValue : kOther);
+    if (g.q1 >= 0) visit(g.q1, g.kind == HS_CX ? kXLike : g.kind == HS_SWAP ? kOther : kValue);
+    std::sort(d.pred[i].begin(), d.pred[i].end());
+    d.pred[i].erase(std::unique(d.pred[i].begin(), d.pred[i].end()), d.pred[i].end());
+    for (int b : d.pred[i]) d.succ[b].push_back(i);
+  }
+  return d;
+}
+
 hs_status plan_sweeps(Plan* p, hs_dtype dtype, bool spec, const SweepSet** out) {
   std::lock_guard<std::mutex> lk(p->mu);
   SweepSet& set = p->sweeps[spec][dtype];
@@ -78,7 +132,18 @@ hs_status plan_sweeps(Plan* p, hs_dtype dtype, bool spec, const SweepSet** out) 
   const uint64_t pad = (uint64_t(1) << std::min(opt.contig, p->n)) - 1;
   if (parts_fit) reduce_plan(p);
   const std::vector<Gate>& gates = p->reduced;
-  const Dag& dag = p->reduced_dag;
+  // the specialized kernels read controls and phases off an amplitude's index:
+  // only what a gate needs in registers binds its sweep
+  opt.conditions = spec;
+  if (spec) opt.fuse2 = false;  // merged ops would need both qubits in registers
+  std::vector<Gate> stand_ins;
+  Dag loose;
+  if (spec && parts_fit) {
+    stand_ins = active_gates(gates);
+    loose = commuting_dag(p->n, gates);
+  }
+  const std::vector<Gate>& cut = spec ? stand_ins : gates;
+  const Dag& dag = spec ? loose : p->reduced_dag;
   std::vector<int32_t> best, part;
   int count = 0;
   double work = 0;  // a matrix gate is 4 instructions an amplitude (compile.cpp), a phase on a quarter 1
@@ -89,13 +154,13 @@ hs_status plan_sweeps(Plan* p, hs_dtype dtype, bool spec, const SweepSet** out) 
   // search: 8-12% fewer sweeps at width 4 (10 ms per 1,000 gates of the random
   // circuit) and 3% fewer again at 16 (20 ms), which sweeps of 2 GiB and more
   // repay in a few runs.
-  const int beam = !spec ? 1 : p->n >= 28 ? 16 : 4;
+  const int beam = !spec ? 1 : p->n >= 31 ? 16 : 4;
   if (parts_fit)
     for (int m : tile_widths(p->n, dtype, spec, opt)) {
       bool fits = true;
-      for (const Gate& g : gates) fits &= __builtin_popcountll(g.mask() | pad) <= m;
+      for (const Gate& g : cut) fits &= __builtin_popcountll(g.mask() | pad) <= m;
       if (!fits) continue;
-      const int c = partition_closure(gates, dag, m, beam, &part, pad);
+      const int c = partition_closure(cut, dag, m, beam, &part, pad, spec);
       if (c <= kWorthwhile * (double)p->parts.size() && c * tile_cost(m, dtype, work / c) < cost) {
         cost = c * tile_cost(m, dtype, work / c);
         count = c;
