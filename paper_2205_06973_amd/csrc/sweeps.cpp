@@ -51,6 +51,14 @@ double tile_cost(int m, hs_dtype dtype, double work) {
   return m >= 13 ? 1.05 + 0.65 * alu : 1.0 + 0.33 * alu;
 }
 
+// A complex64 sweep of more instructions an amplitude than this holds 16
+// amplitudes a lane instead of 32: a stage then takes four bits, for one
+// re-layout more a sweep, but twice the wavefronts overlap loads and
+// arithmetic.  Tiles of 13 qubits, 32 / 16 amplitudes: layered circuit (160
+// instructions and three re-layouts a sweep) 1.33 / 1.22 ms a sweep, random (55,
+// three) 3.87 / 3.72, QFT (30, one) 7.24 / 8.36.
+constexpr double kManyInstructions = 32;
+
 // The plan's reduced gates (p->mu held).
 void reduce_plan(Plan* p) {
   if (!p->reduced.empty()) return;
@@ -172,6 +180,13 @@ hs_status plan_sweeps(Plan* p, hs_dtype dtype, bool spec, const SweepSet** out) 
   std::vector<CompiledPart> comp(count);
   for (int i = 0; i < count; ++i) {
     if (hs_status rc = compile_part(p->n, piece[i], opt, &comp[i])) return rc;
+    if (spec && dtype == HS_C64 && opt.rb == 5 && comp[i].lds_round_trips > 1 && part_work(comp[i]) > kManyInstructions) {
+      CompileOptions narrow = opt;
+      narrow.rb = 4;
+      CompiledPart alt;
+      if (compile_part(p->n, piece[i], narrow, &alt) == HS_OK) comp[i] = std::move(alt);
+      else clear_error();
+    }
     comp[i].launch = opt.launch;
   }
   set.comp.swap(comp);
