@@ -105,12 +105,11 @@ std::string check_partition(const std::vector<Gate>& gates, const Dag& dag,
 struct HostOp {
   int kind, b0, b1;
   double c[32];  // OP_U2: 4 x 4 complex; the others use the first 8
-  // Conditions of the OP_C* and OP_F kinds: a lane or wave coordinate bit of the
+  // Conditions of OP_CPC, OP_CXC and OP_F: a lane or wave coordinate bit of the
   // stage's layout, kOuterBit + a qubit outside the tile, or kNoCond.
   int cond, cond2;
 };
-constexpr int kNoCond = -1;
-constexpr int kOuterBit = 100;
+
 
 // How a part-pass grid walks the tiles of a part.  Workgroup b of a launch
 // runs on XCD b % 8 and each XCD has its own L2; the hardware sustains more
@@ -163,7 +162,7 @@ struct CompileOptions {
                        // into dense 4 x 4 ops where that saves instructions
   // Only the qubits a gate needs as register bits (active_gates) have to be in
   // the tile and in a stage's registers; the others are read off the
-  // amplitude's index.  Gates are reduced ones; specialized kernels only.
+  // amplitude's index.  Gates are reduced ones.
   bool conditions = false;
   bool plain = false;  // apply every one-qubit run whole, where it ends (Plan::plain)
   LaunchShape launch;
@@ -234,8 +233,10 @@ struct Plan {
   std::vector<CompiledPart> comp[2];    // for the interpreter kernel
   bool scompiled[2] = {false, false};
   std::vector<CompiledPart> scomp[2];   // for the specialized kernels
-  std::vector<Gate> reduced;            // reduce_gates(gates) and its DAG, made when
-  Dag reduced_dag;                      // first cut into sweeps or dense pieces
+  // reduce_gates(gates), their stand-ins and their order, made when the plan is
+  // first cut into sweeps or dense pieces
+  std::vector<Gate> reduced, reduced_active;
+  Dag reduced_dag;
   SweepSet sweeps[2][2];                // [specialized][dtype]
   // uploaded descriptors and built kernels per device: [0] of the parts,
   // [1] of the sweeps

@@ -268,10 +268,38 @@ __device__ __forceinline__ void r_u2(const RegV<T, RB>& a, RegV<T, RB>& b, const
   }
 }
 
-// b = op(a).
+// Ops under a condition on a qubit that is no register bit (OP_CPC, OP_CXC, OP_F):
+// `pos` says where its value is found (HostOp::cond); `thr` holds the lane's lane
+// and wave coordinates, `base` the tile's outer index.
+__device__ __forceinline__ bool condition(int pos, uint32_t thr, uint64_t base) {
+  return pos >= kOuterBit ? (base >> (pos - kOuterBit) & 1) != 0 : (thr >> pos & 1u) != 0;
+}
+
+template <typename T, int RB, int B>
+__device__ __forceinline__ void r_cxc(const RegV<T, RB>& a, RegV<T, RB>& b, bool on) {
+#pragma unroll
+  for (int j = 0; j < (1 << RB); ++j) {
+    const int k = j ^ (1 << B);
+    b[2 * j] = on ? a[2 * k] : a[2 * j];
+    b[2 * j + 1] = on ? a[2 * k + 1] : a[2 * j + 1];
+  }
+}
+
+// Multiply by fr + i fi where bit B is set (B = RB: everywhere).
+template <typename T, int RB, int B>
+__device__ __forceinline__ void r_phase(const RegV<T, RB>& a, RegV<T, RB>& b, T fr, T fi) {
+#pragma unroll
+  for (int j = 0; j < (1 << RB); ++j) {
+    if (B == RB || (j & (1 << B))) cmul_at<T, RB>(a, b, j, fr, fi);
+    else cp_at<T, RB>(a, b, j, j);
+  }
+}
+
+// b = op(a).  Returns the descriptors used: a factor's op is followed by the
+// `b1` factors that are multiplied into it first.
 template <typename T, int RB>
-__device__ __forceinline__ void apply_op(const RegV<T, RB>& a, RegV<T, RB>& b,
-                                         const OpDesc<T>* __restrict__ op) {
+__device__ __forceinline__ int apply_op(const RegV<T, RB>& a, RegV<T, RB>& b,
+                                        const OpDesc<T>* __restrict__ op, uint32_t thr, uint64_t base) {
   const int kind = __builtin_amdgcn_readfirstlane(op->kind);
   const int b0 = __builtin_amdgcn_readfirstlane(op->b0);
   const int b1 = __builtin_amdgcn_readfirstlane(op->b1);
@@ -320,8 +348,34 @@ __device__ __forceinline__ void apply_op(const RegV<T, RB>& a, RegV<T, RB>& b,
       } else {
         __builtin_unreachable();
       }
+    case OP_CXC: {
+      const bool on = condition(b1, thr, base);
+      for_bit<RB>(b0, [&](auto B) __attribute__((always_inline)) { r_cxc<T, RB, decltype(B)::value>(a, b, on); });
+      break;
+    }
+    case OP_CPC: {
+      const bool on = condition(b1, thr, base);
+      const T fr = on ? c[0] : T(1), fi = on ? c[1] : T(0);
+      for_bit<RB>(b0, [&](auto B) __attribute__((always_inline)) { r_phase<T, RB, decltype(B)::value>(a, b, fr, fi); });
+      break;
+    }
+    case OP_FA:
+    case OP_GA: {
+      T fr = T(1), fi = T(0);
+      for (int i = 1; i <= b1; ++i) {
+        const int p0 = __builtin_amdgcn_readfirstlane(op[i].b0), p1 = __builtin_amdgcn_readfirstlane(op[i].b1);
+        const bool on = (p0 == kNoCond || condition(p0, thr, base)) && (p1 == kNoCond || condition(p1, thr, base));
+        const T dr = on ? op[i].c[0] : T(1), di = on ? op[i].c[1] : T(0), t = fr;
+        fr = t * dr - fi * di;
+        fi = t * di + fi * dr;
+      }
+      if (kind == OP_FA) r_phase<T, RB, RB>(a, b, fr, fi);
+      else for_bit<RB>(b0, [&](auto B) __attribute__((always_inline)) { r_phase<T, RB, decltype(B)::value>(a, b, fr, fi); });
+      return 1 + b1;
+    }
     default: __builtin_unreachable();
   }
+  return 1;
 }
 
 // LDS swizzle width: the bank window holds 2^sw amplitudes (128 B).
@@ -394,6 +448,7 @@ part_pass_kernel(cplx<T>* __restrict__ st, const IPart* __restrict__ pd,
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const bool active = lane < (1u << pd->lb);
+  const uint32_t thr = lane | wave << pd->lb;
 
   // Tile-independent parts of the addresses.  Bits a layout lacks have zero
   // offsets, so lanes beyond the tile's lane bits stay in bounds.
@@ -420,7 +475,8 @@ part_pass_kernel(cplx<T>* __restrict__ st, const IPart* __restrict__ pd,
   // has 128 VGPRs, and a second tile's registers would spill)
   RegV<T, RB> a, b;
   for (; tile < end; tile += step) {
-    cplx<T>* const base = st + tile_base32(tile, pd->tq, m);
+    const uint64_t outer = tile_base32(tile, pd->tq, m);
+    cplx<T>* const base = st + outer;
     if (active) tile_io<T, RB, false>(base + ld_lane, a, pd->load.reg);
     // ---- execute: stages, re-laid out through LDS where the layout changes
     uint32_t slot = slot0;  // this lane's LDS offset in the current layout
@@ -455,13 +511,13 @@ part_pass_kernel(cplx<T>* __restrict__ st, const IPart* __restrict__ pd,
       // two ops an iteration: a -> b, then b -> a
       const int o1 = e.op_end;
       int o = e.op_begin;
-      for (; o + 1 < o1; o += 2) {
-        apply_op<T, RB>(a, b, ops + o);
-        apply_op<T, RB>(b, a, ops + o + 1);
-      }
-      if (o < o1) {
-        apply_op<T, RB>(a, b, ops + o);
-        a = b;
+      while (o < o1) {
+        o += apply_op<T, RB>(a, b, ops + o, thr, outer);
+        if (o >= o1) {
+          a = b;
+          break;
+        }
+        o += apply_op<T, RB>(b, a, ops + o, thr, outer);
       }
     }
     // ---- scatter (last entry is the store layout)
@@ -1329,6 +1385,11 @@ static OpDesc<T> device_op(const HostOp& h) {
   o.b0 = h.b0;
   o.b1 = h.b1;
   for (int i = 0; i < 32; ++i) o.c[i] = (T)h.c[i];
+  if (h.kind == OP_CPC || h.kind == OP_CXC) o.b1 = h.cond;
+  if (h.kind == OP_F) {
+    o.b0 = h.cond;
+    o.b1 = h.cond2;
+  }
   if (h.kind != OP_U && h.kind != OP_R) return o;
   cd u[4];
   for (int i = 0; i < 4; ++i) u[i] = h.kind == OP_U ? cd(h.c[2 * i], h.c[2 * i + 1]) : cd(h.c[i], 0);
@@ -1388,7 +1449,17 @@ static hs_status upload_plan(const std::vector<CompiledPart>& comp, int dev, Dev
     ip.lb = d.lb;
     ip.n_stages = d.n_stages;
     for (int i = 0; i < kMaxTile; ++i) ip.tq[i] = d.tq[i];
-    for (const HostOp& h : cp.ops) {
+    for (size_t i = 0; i < cp.ops.size(); ++i) {
+      const HostOp& h = cp.ops[i];
+      // a factor's op goes before its factors (see apply_op), with their number
+      if (h.kind == OP_F && (i == 0 || cp.ops[i - 1].kind != OP_F)) {
+        size_t last = i;
+        while (cp.ops[last].kind == OP_F) ++last;
+        OpDesc<T> all = device_op<T>(cp.ops[last]);
+        all.b1 = (int32_t)(last - i);
+        ops.push_back(all);
+      }
+      if (h.kind == OP_FA || h.kind == OP_GA) continue;
       ops.push_back(device_op<T>(h));
     }
     hparts.push_back(d);

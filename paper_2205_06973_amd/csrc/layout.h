@@ -68,8 +68,8 @@ enum OpKind : int32_t {
   OP_H = 13,    // [[1, 1], [1, -1]]
   OP_P = 14,    // [[b, 1], [1, c]]
   OP_W = 15,    // [[1, b], [c, d]]: c = b, c, d
-  // Ops of sweeps on the specialized kernels whose qubits need not all be
-  // register bits (CompileOptions::conditions).  `cond` is where an amplitude's
+  // Ops of sweeps, whose qubits need not all be register bits
+  // (CompileOptions::conditions).  `cond` is where an amplitude's
   // value of the other qubit is found: HostOp::cond.
   OP_CPC = 16,  // multiply by c[0..1] where b0 = 1 and the condition holds
   OP_CXC = 17,  // exchange the pair on b0 where the condition holds
@@ -77,6 +77,9 @@ enum OpKind : int32_t {
   OP_FA = 19,   // multiply all amplitudes by the lane's factor; b0 = 1: it is real
   OP_GA = 20    // the same for the amplitudes with b0 = 1; b1 = 1: it is real
 };
+
+constexpr int kNoCond = -1;
+constexpr int kOuterBit = 100;
 
 template <typename T>
 struct alignas(16) OpDesc {

@@ -1,19 +1,24 @@
 // sweeps.cpp -- the sweeps that hs_simulate runs for a whole plan.
 //
-// A plan's parts are bounded by the k its caller chose; what a sweep of the
-// state can hold is bounded by the kernels' tile.  hs_simulate applies the
-// whole circuit, so it cuts the plan's gates once more, by the closure
-// partitioner with the tile as the limit (the multi-level partition of Sec.
-// IV.B, first level), and runs one sweep of HBM per piece: 33 sweeps instead
-// of 59 parts for the 30-qubit random circuit at k = 7 in complex64, 42 instead
-// of 94 for the 28-qubit layered one at k = 6.  hs_simulate_part keeps to the
-// plan's parts.
+// A plan's parts are bounded by the k its caller chose, and every qubit of a
+// gate counts.  What a sweep of the state can hold is bounded by the kernels'
+// tile, and by less: an amplitude's index tells the value of every qubit, so
+// that CZ and CP, which multiply by a factor the index selects, need no qubit
+// in the tile, and a CX only its target.  hs_simulate applies the whole
+// circuit, so it cuts the plan's gates once more, by the closure partitioner
+// over what each gate needs (active_gates) and the order that binds them
+// (commuting_dag), with the tile as the limit (the multi-level partition of
+// Sec. IV.B, first level), and runs one sweep of HBM per piece.  Sweeps, in
+// place of parts: random circuit on 30 qubits, k = 7, complex64 16 of 59;
+// layered circuit on 28 qubits, k = 6, 31 of 94; QFT on 32 qubits 5 of 45.
+// hs_simulate_part keeps to the plan's parts.
 //
 // Every sweep gathers runs of 128 bytes, one cache line: the tile holds qubits
 // 0..3 (complex64) or 0..2 (complex128) besides the gates' own.  The parts'
 // 512 B to 1 KiB runs are read 6% faster but leave two or three qubits fewer
-// for gates (complex64, random circuit on 30 qubits, tiles of 13: 42 sweeps of
-// 3.29 ms with six padding qubits, 33 of 3.46 ms with four).
+// for gates (complex64, random circuit on 30 qubits, tiles of 13, all qubits
+// counted: 42 sweeps of 3.29 ms with six padding qubits, 33 of 3.46 ms with
+// four).
 #include <algorithm>
 
 #include "hisv_internal.h"
@@ -22,33 +27,20 @@ namespace hisv {
 
 namespace {
 
-// Tile widths to try.  Wide states: 13 qubits (complex64) or 12 (complex128)
-// leave two to five workgroups on a CU, so that the loads of one tile overlap
-// the arithmetic of another; one qubit more hardly overlaps and pays only
-// where it saves enough sweeps and they compute little (see tile_cost).  Small
-// states: a narrower tile, so that there are tiles for the 256 CUs (layered
-// circuit on 17 qubits complex128, tiles of 13 / 12 / 11: 99 / 75 / 68 us).
-// The interpreter is bound by its instructions, not by the sweeps, and loses
-// with 1,024-thread workgroups (25 qubits complex128, 13 / 12 / 11: 8.9 / 7.4 /
-// 7.5 ms).
-std::vector<int> tile_widths(int n, hs_dtype dtype, bool spec, const CompileOptions& opt) {
+// Tile width.  Wide states: 13 qubits (complex64) or 12 (complex128) leave two
+// to five workgroups on a CU, so that the loads of one tile overlap the
+// arithmetic of another; with one qubit more they hardly do (30 qubits, random
+// circuit complex64, 12 / 13 / 14 qubits: 18, 16, 15 sweeps, 65.7 / 61.8 / 72.8
+// ms; complex128, 11 / 12 / 13: 145 / 119 / 134 ms).  Small states: a narrower
+// tile, so that there are tiles for the 256 CUs (layered circuit on 17 qubits
+// complex128, 13 / 12 / 11: 99 / 75 / 68 us).  The interpreter is bound by its
+// instructions, not by the sweeps, and loses with 1,024-thread workgroups (25
+// qubits complex128, 13 / 12 / 11: 8.9 / 7.4 / 7.5 ms).
+int tile_width(int n, hs_dtype dtype, bool spec, const CompileOptions& opt) {
   const bool f32 = dtype == HS_C64;
   const int widest = max_tile_qubits(opt), lo = std::min(widest, f32 ? 11 : 10);
   const int top = std::min(widest, (f32 ? 12 : 11) + (spec ? 1 : 0));
-  const int m = std::min(n, std::max(lo, std::min(top, n - (f32 && spec ? 7 : 8))));
-  std::vector<int> out{m};
-  if (spec && m == top && m + 1 <= widest) out.push_back(m + 1);
-  return out;
-}
-
-// Cost of a sweep over m-qubit tiles in HBM sweeps, `work` vector instructions
-// an amplitude in it.  Measured on 28 and 30 qubits: complex64, tiles of 13 / 14
-// qubits, 1.08 / 1.24 at 24 instructions (random circuit) and 1.38 / 1.81 at 116
-// / 132 (layered); complex128, 12 / 13 qubits, 1.05 / 1.15 and 1.31 / 1.73.
-double tile_cost(int m, hs_dtype dtype, double work) {
-  const double alu = 0.007 * work;
-  if (dtype == HS_C64) return m >= 14 ? 1.12 + 0.75 * alu : 1.02 + 0.43 * alu;
-  return m >= 13 ? 1.05 + 0.65 * alu : 1.0 + 0.33 * alu;
+  return std::min(n, std::max(lo, std::min(top, n - (f32 && spec ? 7 : 8))));
 }
 
 // A complex64 sweep of more instructions an amplitude than this holds 16
@@ -63,7 +55,8 @@ constexpr double kManyInstructions = 32;
 void reduce_plan(Plan* p) {
   if (!p->reduced.empty()) return;
   p->reduced = reduce_gates(p->n, p->gates);
-  p->reduced_dag = build_dag(p->reduced);
+  p->reduced_active = active_gates(p->reduced);
+  p->reduced_dag = commuting_dag(p->n, p->reduced);
 }
 
 // A plan keeps its parts unless regrouping takes at least a tenth of the
@@ -140,41 +133,21 @@ hs_status plan_sweeps(Plan* p, hs_dtype dtype, bool spec, const SweepSet** out) 
   const uint64_t pad = (uint64_t(1) << std::min(opt.contig, p->n)) - 1;
   if (parts_fit) reduce_plan(p);
   const std::vector<Gate>& gates = p->reduced;
-  // the specialized kernels read controls and phases off an amplitude's index:
-  // only what a gate needs in registers binds its sweep
-  opt.conditions = spec;
-  if (spec) opt.fuse2 = false;  // merged ops would need both qubits in registers
-  std::vector<Gate> stand_ins;
-  Dag loose;
-  if (spec && parts_fit) {
-    stand_ins = active_gates(gates);
-    loose = commuting_dag(p->n, gates);
-  }
-  const std::vector<Gate>& cut = spec ? stand_ins : gates;
-  const Dag& dag = spec ? loose : p->reduced_dag;
-  std::vector<int32_t> best, part;
+  // controls and phases are read off an amplitude's index: only what a gate
+  // needs in registers binds its sweep
+  opt.conditions = true;
+  opt.fuse2 = false;  // merged ops would need both qubits in registers
+  std::vector<int32_t> best;
   int count = 0;
-  double work = 0;  // a matrix gate is 4 instructions an amplitude (compile.cpp), a phase on a quarter 1
-  for (const Gate& g : gates) work += g.kind == kMatrixGate ? 4 : g.kind == HS_CP ? 1 : 0;
-  double cost = 1e30;
   // The interpreter's plans, often run once, are cut by the plain closure rule
-  // (1 ms per 1,000 gates); kernels that are built for many runs get the beam
-  // search: 8-12% fewer sweeps at width 4 (10 ms per 1,000 gates of the random
-  // circuit) and 3% fewer again at 16 (20 ms), which sweeps of 2 GiB and more
-  // repay in a few runs.
+  // (2 ms per 1,000 gates); kernels that are built for many runs get the beam
+  // search: 5-12% fewer sweeps at width 4 and up to 5% fewer again at 16, which
+  // sweeps of 16 GiB and more repay in a few runs.
   const int beam = !spec ? 1 : p->n >= 31 ? 16 : 4;
-  if (parts_fit)
-    for (int m : tile_widths(p->n, dtype, spec, opt)) {
-      bool fits = true;
-      for (const Gate& g : cut) fits &= __builtin_popcountll(g.mask() | pad) <= m;
-      if (!fits) continue;
-      const int c = partition_closure(cut, dag, m, beam, &part, pad, spec);
-      if (c <= kWorthwhile * (double)p->parts.size() && c * tile_cost(m, dtype, work / c) < cost) {
-        cost = c * tile_cost(m, dtype, work / c);
-        count = c;
-        best.swap(part);
-      }
-    }
+  const int m = tile_width(p->n, dtype, spec, opt);
+  for (const Gate& g : p->reduced_active) parts_fit &= __builtin_popcountll(g.mask() | pad) <= m;
+  if (parts_fit) count = partition_closure(p->reduced_active, p->reduced_dag, m, beam, &best, pad, true);
+  if (count > kWorthwhile * (double)p->parts.size()) count = 0;
   std::vector<std::vector<Gate>> piece(count);
   for (size_t i = 0; count && i < gates.size(); ++i) piece[best[i]].push_back(gates[i]);
   std::vector<CompiledPart> comp(count);
