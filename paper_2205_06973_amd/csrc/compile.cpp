@@ -931,6 +931,8 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
   out->desc.n_stages = (int)out->stages.size();
   out->desc.lds_bytes = 0;  // set per dtype at upload
   out->lds_round_trips = trips;
+  out->work = 0;
+  for (const HostOp& op : out->ops) out->work += op_work(op);
   return HS_OK;
 }
 
@@ -1031,12 +1033,6 @@ hs_status compile_fused(int n, const std::vector<Gate>& pg, FusedPart* out) {
 
 namespace hisv {
 
-double part_work(const CompiledPart& cp) {
-  double f = 0;
-  for (const HostOp& op : cp.ops) f += op_work(op);
-  return f;
-}
-
 // Relative cost of a part or sweep on the interpreter kernel (one HBM sweep of
 // the state = 1), fitted to the timings of 1,058 of them on 28-qubit complex64
 // and 27-qubit complex128 states (random, layered, dressed-pair and QFT
@@ -1046,7 +1042,7 @@ double part_work(const CompiledPart& cp) {
 // and 0.02 per register op.  A tile that fills the CU overlaps neither with
 // another tile.  Used by AUTO only.
 double lds_part_alu(const CompiledPart& cp, hs_dtype dt) {
-  return (dt == HS_C64 ? 0.007 : 0.006) * part_work(cp) + 0.02 * (double)cp.ops.size();
+  return (dt == HS_C64 ? 0.007 : 0.006) * cp.work + 0.02 * (double)cp.ops.size();
 }
 
 double lds_part_cost(const CompiledPart& cp, hs_dtype dt) {
@@ -1062,7 +1058,7 @@ double lds_part_cost(const CompiledPart& cp, hs_dtype dt) {
 double spec_part_cost(const CompiledPart& cp, hs_dtype dt) {
   const bool f32 = dt == HS_C64;
   const double mem = 0.9 + 0.04 * cp.lds_round_trips;
-  const double alu = 0.007 * part_work(cp);
+  const double alu = 0.007 * cp.work;
   return (cp.desc.m < (f32 ? 14 : 13) ? 1.0 : f32 ? 1.15 : 1.3) * std::cbrt(mem * mem * mem + alu * alu * alu);
 }
 

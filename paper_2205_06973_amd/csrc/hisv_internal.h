@@ -131,6 +131,7 @@ struct CompiledPart {
   std::vector<HostOp> ops;
   int rb_kernel = 0;
   int lds_round_trips = 0;
+  double work = 0;                  // vector instructions an amplitude
   LaunchShape launch;
 };
 
@@ -322,7 +323,6 @@ int fused_launch_shape();
 // relative cost (one HBM sweep = 1) of a part on each path, for AUTO
 double spec_part_cost(const CompiledPart& cp, hs_dtype dt);
 double lds_part_cost(const CompiledPart& cp, hs_dtype dt);
-double part_work(const CompiledPart& cp);  // vector instructions an amplitude
 double lds_part_alu(const CompiledPart& cp, hs_dtype dt);  // its arithmetic alone
 // (by its qubits alone, so that no unitary is built to decide)
 double fused_part_cost(int n, uint64_t mask, hs_dtype dt);

@@ -126,9 +126,11 @@ hs_status plan_sweeps(Plan* p, hs_dtype dtype, bool spec, const SweepSet** out) 
   *out = &set;
   if (set.ready) return HS_OK;
   CompileOptions opt = default_options(dtype, spec);
-  // a part that no tile holds stays an error, which the parts' path reports
+  // a part that no tile holds, or a gate that no stage does, stays an error,
+  // which the parts' path reports
   bool parts_fit = p->parts.size() > 1 && !p->plain(dtype, spec);
   for (uint64_t mask : p->masks) parts_fit &= part_fits(p->n, mask, opt);
+  for (const Gate& g : p->gates) parts_fit &= g.arity() <= opt.rb;
   opt.contig = dtype == HS_C64 ? 4 : 3;
   const uint64_t pad = (uint64_t(1) << std::min(opt.contig, p->n)) - 1;
   if (parts_fit) reduce_plan(p);
@@ -153,7 +155,7 @@ hs_status plan_sweeps(Plan* p, hs_dtype dtype, bool spec, const SweepSet** out) 
   std::vector<CompiledPart> comp(count);
   for (int i = 0; i < count; ++i) {
     if (hs_status rc = compile_part(p->n, piece[i], opt, &comp[i])) return rc;
-    if (spec && dtype == HS_C64 && opt.rb == 5 && comp[i].lds_round_trips > 1 && part_work(comp[i]) > kManyInstructions) {
+    if (spec && dtype == HS_C64 && opt.rb == 5 && comp[i].lds_round_trips > 1 && comp[i].work > kManyInstructions) {
       CompileOptions narrow = opt;
       narrow.rb = 4;
       CompiledPart alt;
