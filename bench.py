@@ -6,9 +6,10 @@ loaded, partitioned (closure partitioner: each part's qubit set chosen so
 that the gates it can take from the current front weigh most; --strategy
 picks Nat, DFS or dagP of Sec. IV.B, or the greedy ready-set partitioner,
 instead) and compiled (the specialized part
-kernels come from the kernel cache after the first pass), every part is
-applied as one in-place Gather-Execute-Scatter sweep of a state resident in
-HBM (Alg. 1), and the FP64 norm is read back.  Default workload: a 33-qubit
+kernels come from the kernel cache after the first pass), the circuit is
+applied as in-place Gather-Execute-Scatter sweeps of a state resident in HBM
+(Alg. 1; hs_simulate cuts the plan's gates into fewer sweeps than the plan has
+parts), and the FP64 norm is read back.  Default workload: a 33-qubit
 random circuit of 1,000 gates drawn uniformly from {H, RZ, RX, CX, CZ},
 complex128 state (the paper's 16 bytes per amplitude, Sec. II.B; 128 GiB),
 acyclic partition with at most k = 7 qubits per part.
@@ -16,7 +17,7 @@ acyclic partition with at most k = 7 qubits per part.
 Prints ONE JSON line on stdout:
   value      gates/s over the timed steps (wall clock, synchronized; host
              ingest, partition and compile included)
-  roofline   the part-pass kernel: algorithmic bytes per launch (read + write
+  roofline   the sweep kernels: algorithmic bytes per launch (read + write
              every amplitude once: 2 * 2^n * bytes/amplitude) / the average
              launch duration from HIP events on the kernel's stream, against
              the 8 TB/s HBM peak; `traffic` from committed rocprofv3 counters
@@ -98,13 +99,13 @@ def part_pass_bytes(n: int, dtype: str) -> int:
 
 
 def spec_kernel_hash(plan, dtype: str) -> str:
-    """Identity of the specialized part kernels a plan runs: the generated
-    source of every part plus the launcher that sizes their grids."""
+    """Identity of the specialized kernels a plan runs: the generated source
+    of every sweep plus the launcher that sizes their grids."""
     h = hashlib.sha256()
     with open(os.path.join(ROOT, "paper_2205_06973_amd", "csrc", "specialize.cpp"), "rb") as fh:
         h.update(fh.read())
-    for i in range(plan.num_parts):
-        h.update(plan.part_source(i, dtype).encode())
+    for i in range(plan.num_sweeps(dtype, "part_spec")):
+        h.update(plan.sweep_source(i, dtype).encode())
     return h.hexdigest()[:16]
 
 
@@ -202,9 +203,9 @@ def run_sweep(args, buf, stream, log):
         sec = timed_plan(st, plan, stream)
         norm = st.norm()
         st.close()
-        P = plan.num_parts
-        gbs = part_pass_bytes(n, dt) * P / sec / 1e9
-        row = {"n": n, "dtype": dt, "k": k, "parts": P, "gates_per_s": len(gates) / sec,
+        W = plan.num_sweeps(dt, "part_spec")
+        gbs = part_pass_bytes(n, dt) * W / sec / 1e9
+        row = {"n": n, "dtype": dt, "k": k, "parts": plan.num_parts, "sweeps": W, "gates_per_s": len(gates) / sec,
                "ms_per_circuit": sec * 1e3, "pass_GBps": gbs, "frac": gbs / HBM_PEAK_GBS,
                "norm_after": norm}
         log(f"[bench] sweep {row}")
@@ -231,8 +232,9 @@ def run_seed_spread(args, buf, stream, log, n=30, dt="c128", k=7, seeds=(0, 1, 2
         plan = hisv.Plan.partition(hisv.Circuit(n, gates), k, args.strategy, seed=sd, trials=args.trials)
         plan.specialize(dt)
         sec = timed_plan(st, plan, stream)
-        gbs = part_pass_bytes(n, dt) * plan.num_parts / sec / 1e9
-        rows.append({"seed": sd, "parts": plan.num_parts, "gates_per_s": len(gates) / sec,
+        W = plan.num_sweeps(dt, "part_spec")
+        gbs = part_pass_bytes(n, dt) * W / sec / 1e9
+        rows.append({"seed": sd, "parts": plan.num_parts, "sweeps": W, "gates_per_s": len(gates) / sec,
                      "pass_GBps": gbs, "frac": gbs / HBM_PEAK_GBS})
     st.close()
     g = [r["gates_per_s"] for r in rows]
@@ -270,8 +272,9 @@ def run_multilevel(args, buf, stream, log):
         norm = st.norm()
         st.close()
         P = plan.num_parts
-        gbs = part_pass_bytes(n, dt) * P / sec / 1e9
-        row = {"workload": name, "n": n, "dtype": dt, "strategy": strat, "tile_qubits": plan.k,
+        W = plan.num_sweeps(dt, "part_spec")
+        gbs = part_pass_bytes(n, dt) * W / sec / 1e9
+        row = {"workload": name, "sweeps": W, "n": n, "dtype": dt, "strategy": strat, "tile_qubits": plan.k,
                "pad_qubits": 6, "parts": P, "gates": len(gates), "gates_per_s": len(gates) / sec,
                "ms_per_circuit": sec * 1e3, "pass_GBps": gbs, "frac": gbs / HBM_PEAK_GBS,
                "norm_after": norm}
@@ -302,12 +305,13 @@ def run_layered(args, buf, stream, log):
         st = hisv.State.wrap_tensor(view, stream)
         plan.specialize(dt)
         row = {"workload": "layered28", "n": n, "dtype": dt, "k": k, "strategy": args.strategy,
-               "parts": P, "gates": G, "passes_saved": G / P}
+               "parts": P, "gates": G, "passes_saved": G / plan.num_sweeps(dt, "part_spec")}
         for mode in ("part_lds", "part_spec", "auto"):
             st.set_basis(0)
             sec = timed_plan(st, plan, stream, steps=3, mode=mode)
-            gbs = part_pass_bytes(n, dt) * P / sec / 1e9
-            row[mode] = {"gates_per_s": G / sec, "ms_per_circuit": sec * 1e3,
+            W = plan.num_sweeps(dt, mode)
+            gbs = part_pass_bytes(n, dt) * W / sec / 1e9
+            row[mode] = {"sweeps": W, "gates_per_s": G / sec, "ms_per_circuit": sec * 1e3,
                          "pass_GBps": gbs, "frac": gbs / HBM_PEAK_GBS, "norm_after": st.norm()}
             if not abs(row[mode]["norm_after"] - 1.0) < 1e-3:
                 raise RuntimeError(f"norm drift in layered case {dt} {mode}")
@@ -355,8 +359,9 @@ def run_dressed(args, buf, stream, log):
         for mode in ("part_spec", "part_fused", "auto"):
             st.set_basis(0)
             sec = timed_plan(st, plan, stream, steps=2, mode=mode)
-            gbs = part_pass_bytes(n, dt) * P / sec / 1e9
-            row[mode] = {"gates_per_s": G / sec, "ms_per_circuit": sec * 1e3,
+            W = plan.num_sweeps(dt, mode)
+            gbs = part_pass_bytes(n, dt) * W / sec / 1e9
+            row[mode] = {"sweeps": W, "gates_per_s": G / sec, "ms_per_circuit": sec * 1e3,
                          "pass_GBps": gbs, "frac": gbs / HBM_PEAK_GBS, "norm_after": st.norm()}
             if not abs(row[mode]["norm_after"] - 1.0) < 1e-3:
                 raise RuntimeError(f"norm drift in dressed case {dt} {mode}")
@@ -392,19 +397,28 @@ def run_qft(buf, stream, log, strategy="closure", trials=16):
                   / (1 << n)) / 2 ** (n / 2)
     out = {"n": n, "dtype": dt, "k": 7, "strategy": strategy, "parts": P, "gates": len(gates)}
     for mode in ("part_spec", "part_fused", "auto"):
+        # the whole circuit in its sweeps; the fused kernels part by part, for
+        # the rate of the 128 x 128 products
+        steps = [lambda: st.simulate(plan, mode)]
+        if mode == "part_fused":
+            steps = [lambda i=i: st.simulate_part(plan, i, "part_fused") for i in range(P)]
+        for f in steps:  # what the first call groups, builds and uploads stays out of the timing
+            f()
         st.set_basis(int(x))
         torch.cuda.synchronize()
-        ev = [torch.cuda.Event(enable_timing=True) for _ in range(P + 1)]
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(len(steps) + 1)]
         ev[0].record(stream)
-        for i in range(P):
-            st.simulate_part(plan, i, mode)
+        for i, f in enumerate(steps):
+            f()
             ev[i + 1].record(stream)
         torch.cuda.synchronize()
-        per = [ev[i].elapsed_time(ev[i + 1]) for i in range(P)]
+        per = [ev[i].elapsed_time(ev[i + 1]) for i in range(len(steps))]
         err = float(np.max(np.abs(st.amplitudes_at(idx) - want)))
         ms = sum(per)
         row = {"ms_per_circuit": ms, "gates_per_s": len(gates) / ms * 1e3,
                "max_abs_err_sampled": err}
+        if mode != "part_fused":
+            row["sweeps"] = plan.num_sweeps(dt, mode)
         if mode == "part_fused":
             w7 = [per[i] for i in range(P) if len(plan.part_unitary(i)[0]) == 7]
             if w7:
@@ -498,7 +512,8 @@ def whole_path(args, n, dt, k, gates, view, stream, steps, warmup, log):
     if not abs(norm - 1.0) < 1e-3:
         # a unitary circuit keeps the norm: anything else is a wrong result
         raise RuntimeError(f"norm after the timed steps is {norm}, not 1")
-    launches = steps * P
+    W = plan.num_sweeps(dt, mode)
+    launches = steps * W
     avg_launch_s = gpu_ms / 1e3 / launches
     bpl = part_pass_bytes(n, dt)
     achieved = bpl / avg_launch_s / 1e9
@@ -514,7 +529,7 @@ def whole_path(args, n, dt, k, gates, view, stream, steps, warmup, log):
     first["break_even_runs"] = ((first["wall_s"] - warm_s) / gain) if gain > 0 else None
     res = {
         "value": G * steps / wall, "ms_per_step": warm_s * 1e3, "plan": plan, "norm": norm,
-        "parts": P, "first_run": first, "gpu_ms": gpu_ms,
+        "parts": P, "sweeps": W, "first_run": first, "gpu_ms": gpu_ms,
         "roofline": {
             "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
@@ -548,8 +563,8 @@ def round_trip_error(args, st, plan, n, k, gates):
 
 def gate_per_pass(st, n, dt, gates, stream, count, part_kernel_s):
     """One sweep per gate on the same state, timed separately for one- and
-    two-qubit gates (a two-qubit sweep leaves a quarter of the amplitudes
-    alone), then projected onto the whole circuit's mix of the two."""
+    two-qubit gates (a two-qubit sweep moves only the amplitudes the gate
+    changes), then projected onto the whole circuit's mix of the two."""
     import torch
     from paper_2205_06973_amd import hisv
     one = [g for g in gates if g[2] < 0][:count]
@@ -771,8 +786,8 @@ def main() -> int:
             "workload": (f"random{n}: {n}-qubit random circuit, {G} gates uniform over "
                          f"{{H,RZ,RX,CX,CZ}}, {state_name} state ({bpl // 2 / 2**30:.0f} GiB), "
                          f"{args.strategy.upper()} partition k={args.k}"),
-            "n": n, "gates": G, "k": args.k, "parts": P, "strategy": args.strategy,
-            "state": state_name, "mode": args.mode, "passes_saved": G / P,
+            "n": n, "gates": G, "k": args.k, "parts": P, "sweeps": head["sweeps"], "strategy": args.strategy,
+            "state": state_name, "mode": args.mode, "passes_saved": G / head["sweeps"],
         },
         "roofline": head["roofline"],
         "first_run": head["first_run"],
@@ -787,7 +802,7 @@ def main() -> int:
     if args.gpp_gates > 0:
         gpp = gate_per_pass(st, n, dt, gates, stream, args.gpp_gates,
                             head["gpu_ms"] / 1e3 / args.steps)
-        gpp["passes_saved"] = G / P
+        gpp["passes_saved"] = G / head["sweeps"]
         gpp["speedup_partitioned"] = out["value"] / gpp["gates_per_s"]
         out["gate_per_pass"] = gpp
         log(f"[bench] gate-per-pass: {gpp}")
