@@ -524,9 +524,8 @@ void fold_scalar(const cl& S, std::vector<HostOp>* ops) {
   else (*ops)[at].kind = OP_D, (*ops)[at].c[0] = (*ops)[at].c[2] = 1, (*ops)[at].c[1] = (*ops)[at].c[3] = 0;
 }
 
-// Register-stage cut: seeded DFS orders tried per part.
+// Register-stage cut: the seed of the orders tried per part.
 constexpr uint64_t kStageSeed = 0x5eed;
-constexpr int kStageTrials = 32;
 
 }  // namespace
 
@@ -583,8 +582,8 @@ hs_status compile_part(int n, const std::vector<Gate>& pg, const CompileOptions&
     if (g.arity() > rb) return fail(HS_E_UNSUPPORTED, "gate wider than the register stage");
   std::vector<int32_t> stage_of, greedy_of;
   const Dag pdag = opt.conditions ? commuting_dag(n, pg) : build_dag(pg);
-  int nst = partition_dfs(act, pdag, rb, kStageSeed, kStageTrials, &stage_of);
-  const int ngr = partition_greedy(act, pdag, rb, kStageSeed, kStageTrials, &greedy_of);
+  int nst = partition_dfs(act, pdag, rb, kStageSeed, opt.stage_trials, &stage_of);
+  const int ngr = partition_greedy(act, pdag, rb, kStageSeed, opt.stage_trials, &greedy_of);
   if (ngr < nst) {
     nst = ngr;
     stage_of.swap(greedy_of);

@@ -165,6 +165,7 @@ struct CompileOptions {
   // the tile and in a stage's registers; the others are read off the
   // amplitude's index.  Gates are reduced ones.
   bool conditions = false;
+  int stage_trials = 32;  // orders tried for the cut into register stages
   bool plain = false;  // apply every one-qubit run whole, where it ends (Plan::plain)
   LaunchShape launch;
 };
