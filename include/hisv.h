@@ -120,10 +120,11 @@ typedef enum {
  *                    (the non-hierarchical case of Sec. III.B);
  *   PART_LDS      -- one sweep per part or piece; each runs gate by gate on
  *                    register-resident sub-states, staged through LDS;
- *   PART_FUSED    -- one sweep per part; each part's gates are multiplied
- *                    into one dense 2^w x 2^w unitary applied on matrix cores;
- *   AUTO          -- the cheapest by a cost model: the pieces gate by gate, or
- *                    per part PART_FUSED or the gate-by-gate kernel;
+ *   PART_FUSED    -- one sweep per part, or per piece of six qubits where
+ *                    those are cheaper; each one's gates are multiplied into
+ *                    one dense 2^w x 2^w unitary applied on matrix cores;
+ *   AUTO          -- the cheapest by a cost model: the pieces gate by gate,
+ *                    PART_FUSED's pieces, or per part PART_FUSED or the gate-by-gate kernel;
  *                    PART_SPEC's kernels where they have been built for the
  *                    state's dtype and device, else PART_LDS's;
  *   PART_SPEC     -- sweeps as in PART_LDS, with each one's kernel
@@ -156,8 +157,9 @@ hs_status hs_device_count(int* out);
 /* Layout knobs read when a plan is next compiled (plans already compiled
  * keep theirs): "rb_c64" / "rb_c128" = register bits per lane (2^rb
  * amplitudes each; 1..4 / 1..3 for the interpreter kernel, 1..5 for the
- * specialized kernels); "contig" = the tile always holds qubits 0..contig-1
- * (0..8, default 6); "min_run_c64" / "min_run_c128" = gather and scatter straight in a
+ * specialized kernels); "contig" = a part's tile always holds qubits
+ * 0..contig-1 (0..8, default 6; the pieces that hs_simulate cuts always hold
+ * 0..3 / 0..2); "min_run_c64" / "min_run_c128" = gather and scatter straight in a
  * stage's layout when its lanes still cover qubits 0..min_run-1, instead of
  * re-laying out through LDS (0..6; 6 = only fully contiguous 64-amplitude
  * runs); "min_tile" (0..16) = pad every tile with the lowest free qubits up
@@ -165,7 +167,7 @@ hs_status hs_device_count(int* out);
  * capped at the kernel's widest tile); "fuse2" (0/1; default 1 for the
  * interpreter, 0 for the specialized kernels) = merge a two-qubit gate and
  * the dense one-qubit gates around it into one 4 x 4 op where that saves
- * instructions.  Launch shape of the part kernels: "xcd" (0/1) = each of the 8
+ * instructions (parts; not the pieces).  Launch shape of the part kernels: "xcd" (0/1) = each of the 8
  * XCDs sweeps one contiguous eighth of the tiles; "grid" = 0 for one
  * workgroup per tile, g in 1..64 for a persistent grid of g x the resident
  * workgroups per CU; "spec_prefetch" (0/1) = a persistent grid of the
@@ -173,10 +175,12 @@ hs_status hs_device_count(int* out);
  * "spec_lds_limit_kib" (16..160, default 64) = the specialized kernels run
  * each LDS re-layout in 2 or 4 rounds, over half or a quarter of the tile,
  * when the tile's LDS image is larger; "fused_shape" (-1..2, default -1) =
- * launch shape of the fused kernels of 4- and 5-qubit parts: 0 = one group
- * of tiles per workgroup, 1 = a persistent grid whose waves issue the next
- * group's loads before the current group's products, 2 = a persistent grid
- * of the plain kernel, -1 = the measured best for the width and precision.
+ * how the fused kernels of 4- and 5-qubit parts run: -1 = the fastest measured
+ * for the width and precision (five qubits: the unitary in LDS, each workgroup
+ * a run of tile groups), else the kernel that keeps the unitary in registers
+ * or reads it from L2, 0 = one group of tiles per workgroup, 1 = a persistent
+ * grid whose waves issue the next group's loads before the current group's
+ * products, 2 = a persistent grid without that.
  * Host side: "host_threads" (0..64, default 0 = up to 8 as the host has
  * them) = threads a CLOSURE beam search may use; its plans are the same
  * for every value.  "serve_chunk" (1..4096, default 8) = part-passes a

@@ -54,7 +54,7 @@ def _short(name: str) -> str:
     base = name.split("(")[0]
     if "part_pass_spec" in base:  # one kernel per part (part_pass_spec_<i>): one row
         return "part_pass_spec"
-    for tag in ("part_pass_kernel", "fused_pass_kernel", "gate_pass_1q",
+    for tag in ("part_pass_kernel", "fused_pass_kernel", "fused_lds_kernel", "gate_pass_1q", "gate_pass_diag",
                 "gate_pass_2q", "set_basis_kernel", "norm_partial", "norm_final", "readout_kernel",
                 "gather_kernel", "copy_probe_kernel"):
         if tag in base:
