@@ -106,3 +106,21 @@ def test_only_diagonals(tmp_path):
     gates = [(("cz", "cp")[i % 2], i % n, (i * 5 + 1) % n, (0.2 * i,) if i % 2 else ())
              for i in range(60) if i % n != (i * 5 + 1) % n] + [("s", q, -1, ()) for q in range(n)]
     run(n, gates, "c64", 3, tmp_path)
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+def test_gate_wider_than_a_stage_is_refused(dtype):
+    """With one register bit a two-qubit gate fits no stage: the parts refuse
+    it, and no sweep takes it (CX and CZ, whose conditions would need fewer)."""
+    n = 14
+    gates = [(("cx", "cz")[i % 2], i % n, (i * 5 + 1) % n, ()) for i in range(40) if i % n != (i * 5 + 1) % n]
+    plan = hisv.Plan.partition(hisv.Circuit(n, gates), 5, "dfs")
+    default = {"c64": 5, "c128": 4}[dtype]
+    hisv.hs_tune(f"spec_rb_{dtype}", 1)
+    try:
+        assert plan.num_sweeps(dtype, "part_spec") == plan.num_parts
+        for source in (plan.part_source, plan.sweep_source):
+            with pytest.raises(hisv.HisvError, match="HS_E_UNSUPPORTED"):
+                source(0, dtype)
+    finally:
+        hisv.hs_tune(f"spec_rb_{dtype}", default)
