@@ -19,8 +19,8 @@
 // the load and store layouts, neighbouring global addresses).
 //
 // Runs of one-qubit gates on the same bit with no other gate on that bit in
-// between are multiplied into one 2x2 in FP64 (gates on different bits
-// commute, so the product can be applied where the run ends), and the 2x2
+// between are multiplied into one 2x2 in extended precision (gates on different
+// bits commute, so the product can be applied where the run ends), and the 2x2
 // is split so that as little of it as possible runs (split_gate below).
 #include <algorithm>
 #include <array>

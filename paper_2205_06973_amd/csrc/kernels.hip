@@ -6,8 +6,10 @@
 //                      part's register stages (LDS re-layouts in between) and
 //                      scatters the tile back -- one HBM read and one write
 //                      per amplitude per part.
-//   gate_pass_1q/2q    the non-hierarchical case (Sec. III.A-B): one full
-//                      sweep of the state per gate.
+//   fused_pass_kernel, fused_lds_kernel  a part's dense unitary on the matrix
+//                      cores.
+//   gate_pass_1q/diag/2q  the non-hierarchical case (Sec. III.A-B): one sweep
+//                      per gate, over the amplitudes it changes.
 //   set_basis, norm, probabilities/amplitude readout, copy probe.
 //
 // Amplitudes are interleaved complex (float2 / double2), index bit q =
